@@ -60,7 +60,10 @@ struct pm_ctx {
   KernelGeom kg{};
   SortBufs sb{};
   PieceBufs pb{};
-  int piece_ext = 0;          // compiled ball shape of the tile-piece kernels, 0: none
+  int piece_ext = 0;          // compiled ball shape of the tile-piece deposit, 0: none
+  int plan_ext = 0;           // the ball's extent if the tile-piece gather takes it, 0: none
+  int* rowtab = nullptr;      // rows of the ball
+  int nrows = 0;
   int64_t perm_n = -1;        // sb.perm is a permutation of [0, perm_n) from the last sort
   int npartials = 0;
   hipGraphExec_t step_graph = nullptr;  // one captured pm_step (pm_step_capture)
@@ -167,6 +170,19 @@ static std::vector<int> make_ball(double R) {
   return out;
 }
 
+// Rows (dy, dz) of the ball with the half-width h of their cells |dx| <= h.
+static std::vector<int> make_rows(double R) {
+  std::vector<int> out;
+  const int m = (int)floor(R);
+  for (int dz = -m; dz <= m; ++dz)
+    for (int dy = -m; dy <= m; ++dy) {
+      int h = -1;
+      while ((double)((h + 1) * (h + 1) + dy * dy + dz * dz) < R * R) ++h;
+      if (h >= 0) out.push_back((dy + 16) | ((dz + 16) << 8) | (h << 16));
+    }
+  return out;
+}
+
 static bool need_residual(const pm_params& p) { return (p.flags & PM_F_RESIDUAL) || p.tol > 0.0; }
 
 // Device memory of a context: one region (the caller's workspace or a single
@@ -192,18 +208,22 @@ static void derive_sizes(pm_ctx* c, const pm_params* p, int64_t max_particles) {
   c->P = pm_spectrum_pitch(p->n_pad);
   c->max_particles = max_particles;
   c->nball = (int)make_ball(p->cutoff * p->sigma).size();
+  c->nrows = (int)make_rows(p->cutoff * p->sigma).size();
   c->npartials = x_blocks(c->N) > z_blocks(c->N) ? x_blocks(c->N) : z_blocks(c->N);
   // The tile-piece kernels are compiled for the balls |d|^2 < 16 and < 36
   // (radius 4 sigma at sigma = 1 and 1.5 cells): any R^2 in (15, 16] or
   // (35, 36] gives the same integer cells.
   const double R2 = (p->cutoff * p->sigma) * (p->cutoff * p->sigma);
   c->piece_ext = (R2 > 15.0 && R2 <= 16.0) ? 3 : (R2 > 35.0 && R2 <= 36.0) ? 5 : 0;
+  // A ball of extent up to 8 reaches only the tiles next to its own.
+  const int ext = ball_extent(p->cutoff * p->sigma);
+  c->plan_ext = (ext >= 1 && ext <= 8) ? ext : 0;
   c->pb.cap = 0;
   if (c->piece_ext) {
     const int64_t N = c->N;
     const int64_t ntiles = (N / 8) * (N / 8) * (N / 8);
     const int64_t mp = max_particles > 0 ? max_particles : 1;
-    const int64_t most = max_pieces(ntiles, mp);
+    const int64_t most = max_pieces(ntiles, mp, piece_size(ext));
     const int64_t te = 8 + 2 * c->piece_ext;
     const int64_t by_bytes = ((int64_t)2 << 30) / (te * te * te * 8);      // 2 GB of staging
     c->pb.cap = (int)(most < by_bytes ? most : by_bytes);
@@ -230,17 +250,17 @@ static size_t carve(pm_ctx* c, Carver& cv) {
   c->kt = cv.take<float>(N);
   c->kap = cv.take<float>(N);
   c->ball = cv.take<int>((size_t)c->nball);
-  c->ibuf = cv.take<int>(4 * mp + 2 * (ntiles + 1) + nb + 16);
+  c->ibuf = cv.take<int>(4 * mp + 2 * (ntiles + 1) + 3 * nb + 16);
   c->snorm = cv.take<double>(mp);
-  if (c->piece_ext) {
+  c->rowtab = cv.take<int>((size_t)c->nrows);
+  if (c->plan_ext) {
     c->pb.pc_off = cv.take<int>(ntiles + 1);
-    c->pb.flag = cv.take<int>(ntiles);
     c->pb.list_off = cv.take<int>(ntiles + 1);
     c->pb.list = cv.take<int>(ntiles);
-    c->pb.ptile = cv.take<int>((size_t)max_pieces((int64_t)ntiles, (int64_t)mp));
+    c->pb.ptile = cv.take<int>((size_t)max_pieces((int64_t)ntiles, (int64_t)mp, piece_size(c->plan_ext)));
     c->pb.counter = cv.take<int>(16);
     c->pb.tmax = cv.take<unsigned>(ntiles);
-    c->pb.stage = cv.take<long long>(piece_stage_cells(c->piece_ext, c->pb.cap));
+    if (c->piece_ext) c->pb.stage = cv.take<long long>(piece_stage_cells(c->piece_ext, c->pb.cap));
   }
   return (cv.off + 255) & ~(size_t)255;
 }
@@ -285,7 +305,7 @@ pm_status pm_create(const pm_params* p, int64_t max_particles, void* workspace, 
   const int N = c->N;
   const size_t C = (size_t)N * N * c->P;
   const double Rb = p->cutoff * p->sigma;
-  std::vector<int> ball = make_ball(Rb);
+  std::vector<int> ball = make_ball(Rb), rows = make_rows(Rb);
   const int ext = ball_extent(Rb);
   const size_t lds_need = sizeof(float) * (((ball.size() + 3) & ~(size_t)3) + (size_t)(8 + 2 * (ext + 1)) *
                                                                                    (8 + 2 * (ext + 1)) * (8 + 2 * (ext + 1)));
@@ -344,6 +364,7 @@ pm_status pm_create(const pm_params* p, int64_t max_particles, void* workspace, 
   CCHK(hipMemcpyAsync(c->kt, kt.data(), N * sizeof(float), hipMemcpyHostToDevice, c->st));
   CCHK(hipMemcpyAsync(c->kap, kap.data(), N * sizeof(float), hipMemcpyHostToDevice, c->st));
   CCHK(hipMemcpyAsync(c->ball, ball.data(), ball.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
+  CCHK(hipMemcpyAsync(c->rowtab, rows.data(), rows.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
 
   c->fg.N = N;
   c->fg.P = c->P;
@@ -373,6 +394,10 @@ pm_status pm_create(const pm_params* p, int64_t max_particles, void* workspace, 
     c->kg.private_tiles = (4 * te * te * te * sizeof(float) <= 96 * 1024) ? 1 : 0;
   }
   c->kg.piece_ext = c->piece_ext;
+  c->kg.plan_ext = c->plan_ext;
+  c->kg.piece = piece_size(ext);
+  c->kg.nrows = c->nrows;
+  c->kg.rows = c->rowtab;
 
   const size_t mp = (size_t)(max_particles > 0 ? max_particles : 1);
   const size_t nb = ((size_t)ntiles + 1023) / 1024;
@@ -383,7 +408,7 @@ pm_status pm_create(const pm_params* p, int64_t max_particles, void* workspace, 
   c->sb.skey = ib; ib += mp;
   c->sb.counts = ib; ib += ntiles + 1;
   c->sb.offsets = ib; ib += ntiles + 1;
-  c->sb.blocksums = ib; ib += nb;
+  c->sb.blocksums = ib; ib += 3 * nb;
   c->sb.flags = ib;
   c->sb.ntiles = ntiles;
   CCHK(fill_zero(reinterpret_cast<float*>(c->sb.flags), 16, c->st));
@@ -639,9 +664,8 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
 // Tile sort of the particles, then (tile-piece kernels) the piece plan.
 static hipError_t sort_and_plan(pm_ctx* c, const float* pos, int64_t n) {
   Timed t(c, PM_T_SORT);
-  hipError_t e = sort_particles(c->kg, c->sb, pos, n, c->st, c->perm_n == n);
+  const hipError_t e = sort_particles(c->kg, c->sb, pos, n, c->st, c->perm_n == n, c->plan_ext ? &c->pb : nullptr);
   c->perm_n = (e == hipSuccess) ? n : -1;
-  if (e == hipSuccess && c->piece_ext && n > 0) e = piece_plan(c->pb, c->sb, c->N, c->st);
   return e;
 }
 
@@ -655,7 +679,7 @@ static hipError_t deposit_any(pm_ctx* c, const float* pos, const float* mass, in
 static hipError_t gather_any(pm_ctx* c, const float* phi, float* pos, float* vel, float* acc, int64_t n,
                              float dt_kick, float dt_drift, int mode, const double* s_store) {
   Timed t(c, PM_T_GATHER);
-  if (c->piece_ext) return gather_pieces(c->kg, c->sb, c->pb, phi, pos, vel, acc, n, dt_kick, dt_drift, mode, c->st);
+  if (c->plan_ext) return gather_pieces(c->kg, c->sb, c->pb, phi, pos, vel, acc, n, dt_kick, dt_drift, mode, c->st);
   return gather_sorted(c->kg, c->sb, phi, pos, vel, acc, n, dt_kick, dt_drift, mode, s_store, c->st);
 }
 

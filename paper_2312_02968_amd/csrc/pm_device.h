@@ -80,6 +80,18 @@ struct Dft<4, INV> {
   }
 };
 
+// Central pixel floor(u + 1/2) and sub-pixel offset (pixel minus position) of
+// a coordinate x, u = x / s in cells.  The sort and the particle kernels have
+// to agree on the pixel to the last bit, so the multiply and the add are kept
+// apart (no fused multiply-add) wherever the pixel is formed.
+__device__ __forceinline__ int central_pixel(float x, double inv_s, float* f) {
+#pragma clang fp contract(off)
+  const double u = (double)x * inv_s;
+  const double c = floor(u + 0.5);
+  if (f) *f = (float)(c - u);
+  return (int)c;
+}
+
 // Radix plan of a length-L transform: radix of stage st (0-based).
 template <int L>
 struct Plan;

@@ -64,17 +64,10 @@ __device__ __forceinline__ float ball_weight(const KernelGeom& kg, const Part& p
 __device__ __forceinline__ Part particle_setup(const KernelGeom& kg, const int* __restrict__ ball_lds, float px,
                                                float py, float pz, int lane, bool with_sum = true) {
   Part p;
-  const double ux = (double)px * kg.inv_s;
-  const double uy = (double)py * kg.inv_s;
-  const double uz = (double)pz * kg.inv_s;
-  const double cxd = floor(ux + 0.5), cyd = floor(uy + 0.5), czd = floor(uz + 0.5);
   const int half = kg.N / 2;
-  p.cx = wrapi((int)cxd + half, kg.N);
-  p.cy = wrapi((int)cyd + half, kg.N);
-  p.cz = wrapi((int)czd + half, kg.N);
-  p.fx = (float)(cxd - ux);
-  p.fy = (float)(cyd - uy);
-  p.fz = (float)(czd - uz);
+  p.cx = wrapi(central_pixel(px, kg.inv_s, &p.fx) + half, kg.N);
+  p.cy = wrapi(central_pixel(py, kg.inv_s, &p.fy) + half, kg.N);
+  p.cz = wrapi(central_pixel(pz, kg.inv_s, &p.fz) + half, kg.N);
   p.S = 0.0;
   if (!with_sum || kg.analytic) return p;
   double acc = 0.0;
@@ -118,7 +111,7 @@ __global__ __launch_bounds__(256) void k_keys(const float* __restrict__ pos, int
   if (valid) {
     int c[3];
     for (int a = 0; a < 3; ++a) {
-      const int ci = (int)floor((double)pos[3 * i + a] * inv_s + 0.5) + half;
+      const int ci = central_pixel(pos[3 * i + a], inv_s, nullptr) + half;
       out |= (ci - ext < half - nphys / 2) || (ci + ext > half + nphys / 2 - 1);
       c[a] = wrapi(ci, N);
     }
@@ -144,54 +137,134 @@ __global__ __launch_bounds__(256) void k_keys(const float* __restrict__ pos, int
   if (outs && lane == __ffsll((long long)outs) - 1) atomicAdd(&flags[0], __popcll(outs));
 }
 
-// Exclusive scan of counts[0..n) into offsets[0..n]; blocks of 1024 entries.
-__global__ __launch_bounds__(1024) void k_scan_local(const int* __restrict__ counts, int n, int* offsets,
-                                                     int* blocksums) {
-  __shared__ int s[1024];
-  const int i = blockIdx.x * 1024 + threadIdx.x;
-  const int v = (i < n) ? counts[i] : 0;
-  s[threadIdx.x] = v;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int t = (threadIdx.x >= o) ? s[threadIdx.x - o] : 0;
-    __syncthreads();
-    s[threadIdx.x] += t;
-    __syncthreads();
+// Exclusive scans over the tiles, in blocks of 1024: the particle counts
+// (offsets), and with PLAN also the pieces per tile (pc_off) and whether the
+// tile receives staged cells (list_off), i.e. whether one of its 27 periodic
+// neighbours holds particles.  One scan of all three in three launches: the
+// plan's cost in a small box is its launches.
+template <int NV>
+__device__ __forceinline__ void block_scan(const int* v, int* ex, int* total) {
+  __shared__ int ws[NV][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int inc[NV];
+#pragma unroll
+  for (int c = 0; c < NV; ++c) {
+    int x = v[c];
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    inc[c] = x;
+    if (lane == 63) ws[c][wave] = x;
   }
-  if (i < n) offsets[i] = s[threadIdx.x] - v;
-  if (threadIdx.x == 1023) blocksums[blockIdx.x] = s[1023];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NV; ++c) {
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      before += w < wave ? ws[c][w] : 0;
+      all += ws[c][w];
+    }
+    ex[c] = before + inc[c] - v[c];
+    total[c] = all;
+  }
 }
 
-// Exclusive scan of up to 4096 block sums in one block; total into *total.
-__global__ __launch_bounds__(1024) void k_scan_top(int* blocksums, int nb, int* total) {
-  __shared__ int s[1024];
-  int loc[4];
-  int sum = 0;
-  for (int j = 0; j < 4; ++j) {
-    const int i = threadIdx.x * 4 + j;
-    loc[j] = (i < nb) ? blocksums[i] : 0;
-    sum += loc[j];
-  }
-  s[threadIdx.x] = sum;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int t = (threadIdx.x >= o) ? s[threadIdx.x - o] : 0;
-    __syncthreads();
-    s[threadIdx.x] += t;
-    __syncthreads();
-  }
-  int run = s[threadIdx.x] - sum;
-  for (int j = 0; j < 4; ++j) {
-    const int i = threadIdx.x * 4 + j;
-    if (i < nb) blocksums[i] = run;
-    run += loc[j];
-  }
-  if (threadIdx.x == 1023) *total = s[1023];
+__device__ __forceinline__ bool near_matter(const int* __restrict__ counts, int t, int nt) {
+  const int m = nt - 1, tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
+  int any = 0;
+  for (int dz = -1; dz <= 1; ++dz)
+    for (int dy = -1; dy <= 1; ++dy)
+      for (int dx = -1; dx <= 1; ++dx) any |= counts[(((tz + dz) & m) * nt + ((ty + dy) & m)) * nt + ((tx + dx) & m)];
+  return any > 0;
 }
 
-__global__ __launch_bounds__(1024) void k_scan_add(int* offsets, int n, const int* __restrict__ blocksums) {
-  const int i = blockIdx.x * 1024 + threadIdx.x;
-  if (i < n) offsets[i] += blocksums[blockIdx.x];
+struct PlanOut {
+  int* offsets;
+  int* pc_off;
+  int* list_off;
+  int* list;
+  int* ptile;
+  int* counter;
+  unsigned* tmax;
+};
+
+template <bool PLAN>
+__global__ __launch_bounds__(1024) void k_scan_local(const int* __restrict__ counts, int n, int nt, int piece,
+                                                     PlanOut o, int* blocksums) {
+  constexpr int NV = PLAN ? 3 : 1;
+  const int t = blockIdx.x * 1024 + threadIdx.x;
+  int v[NV] = {}, ex[NV], total[NV];
+  if (t < n) {
+    v[0] = counts[t];
+    if constexpr (PLAN) {
+      v[1] = (v[0] + piece - 1) / piece;
+      v[2] = near_matter(counts, t, nt);
+    }
+  }
+  block_scan<NV>(v, ex, total);
+  if (t < n) {
+    o.offsets[t] = ex[0];
+    if constexpr (PLAN) {
+      o.pc_off[t] = ex[1];
+      o.list_off[t] = ex[2];
+    }
+  }
+  if (threadIdx.x == 0)
+    for (int c = 0; c < NV; ++c) blocksums[c * gridDim.x + blockIdx.x] = total[c];
+}
+
+// Exclusive scan of up to 4096 block sums of each kind in one block; the
+// totals go to the last entries.
+template <bool PLAN>
+__global__ __launch_bounds__(1024) void k_scan_top(int* blocksums, int nb, int n, PlanOut o) {
+  constexpr int NV = PLAN ? 3 : 1;
+  int loc[NV][4], sum[NV], ex[NV], total[NV];
+#pragma unroll
+  for (int c = 0; c < NV; ++c) {
+    sum[c] = 0;
+    for (int j = 0; j < 4; ++j) {
+      const int i = threadIdx.x * 4 + j;
+      loc[c][j] = i < nb ? blocksums[c * nb + i] : 0;
+      sum[c] += loc[c][j];
+    }
+  }
+  block_scan<NV>(sum, ex, total);
+#pragma unroll
+  for (int c = 0; c < NV; ++c)
+    for (int j = 0; j < 4; ++j) {
+      const int i = threadIdx.x * 4 + j;
+      if (i < nb) blocksums[c * nb + i] = ex[c];
+      ex[c] += loc[c][j];
+    }
+  if (threadIdx.x == 0) {
+    o.offsets[n] = total[0];
+    if constexpr (PLAN) {
+      o.pc_off[n] = total[1];
+      o.list_off[n] = total[2];
+      o.counter[0] = o.counter[1] = 0;
+    }
+  }
+}
+
+// Adds the block sums; with PLAN also the tile of every piece, the list of the
+// tiles that receive staged cells, and the tiles' mass maxima set to zero.
+template <bool PLAN>
+__global__ __launch_bounds__(1024) void k_scan_add(int n, const int* __restrict__ blocksums,
+                                                   const int* __restrict__ counts, int nt, int piece, PlanOut o) {
+  const int t = blockIdx.x * 1024 + threadIdx.x;
+  if (t >= n) return;
+  o.offsets[t] += blocksums[blockIdx.x];
+  if constexpr (PLAN) {
+    const int nb = gridDim.x;
+    const int q0 = o.pc_off[t] + blocksums[nb + blockIdx.x];
+    o.pc_off[t] = q0;
+    const int q1 = q0 + (counts[t] + piece - 1) / piece;
+    for (int q = q0; q < q1; ++q) o.ptile[q] = t;
+    if (near_matter(counts, t, nt)) o.list[o.list_off[t] + blocksums[2 * nb + blockIdx.x]] = t;
+    o.tmax[t] = 0u;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_scatter(int64_t n, const int* __restrict__ keys,
@@ -572,16 +645,27 @@ hipError_t fill_zero(float* p, long long count, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t scan_exclusive(const int* in, int n, int* out, int* blocksums, hipStream_t st) {
-  const int nb = (n + 1023) / 1024;
-  hipLaunchKernelGGL(k_scan_local, dim3(nb), dim3(1024), 0, st, in, n, out, blocksums);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, st, blocksums, nb, out + n);
-  hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(1024), 0, st, out, n, blocksums);
+template <bool PLAN>
+static hipError_t scan_tiles(const KernelGeom& kg, const SortBufs& sb, const PieceBufs* pb, hipStream_t st) {
+  const int n = sb.ntiles, nb = (n + 1023) / 1024, nt = kg.N / kTile;
+  PlanOut o{};
+  o.offsets = sb.offsets;
+  if constexpr (PLAN) {
+    o.pc_off = pb->pc_off;
+    o.list_off = pb->list_off;
+    o.list = pb->list;
+    o.ptile = pb->ptile;
+    o.counter = pb->counter;
+    o.tmax = pb->tmax;
+  }
+  hipLaunchKernelGGL(k_scan_local<PLAN>, dim3(nb), dim3(1024), 0, st, sb.counts, n, nt, kg.piece, o, sb.blocksums);
+  hipLaunchKernelGGL(k_scan_top<PLAN>, dim3(1), dim3(1024), 0, st, sb.blocksums, nb, n, o);
+  hipLaunchKernelGGL(k_scan_add<PLAN>, dim3(nb), dim3(1024), 0, st, n, sb.blocksums, sb.counts, nt, kg.piece, o);
   return hipGetLastError();
 }
 
 hipError_t sort_particles(const KernelGeom& kg, const SortBufs& sb, const float* pos, int64_t n,
-                          hipStream_t st, bool prev_order) {
+                          hipStream_t st, bool prev_order, const PieceBufs* pb) {
   hipError_t e = fill_zero(reinterpret_cast<float*>(sb.counts), sb.ntiles + 1, st);
   if (e != hipSuccess) return e;
   if (n > 0) {
@@ -589,7 +673,7 @@ hipError_t sort_particles(const KernelGeom& kg, const SortBufs& sb, const float*
                        kg.inv_s, kg.ext, prev_order ? sb.perm : nullptr, sb.keys, sb.rank, sb.counts, sb.flags);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = scan_exclusive(sb.counts, sb.ntiles, sb.offsets, sb.blocksums, st)) != hipSuccess) return e;
+  if ((e = pb ? scan_tiles<true>(kg, sb, pb, st) : scan_tiles<false>(kg, sb, nullptr, st)) != hipSuccess) return e;
   if (n > 0) {
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, sb.keys, sb.rank,
                        sb.offsets, sb.perm, sb.skey);

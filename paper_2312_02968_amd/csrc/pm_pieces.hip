@@ -53,7 +53,11 @@ constexpr int kNT = 256;
 #ifndef PM_GATHER_NT
 #define PM_GATHER_NT 128
 #endif
-constexpr int kDepNT = PM_DEPOSIT_NT, kGatNT = PM_GATHER_NT;
+#ifndef PM_GATHER_NT_WIDE
+#define PM_GATHER_NT_WIDE 256
+#endif
+constexpr int kDepNT = PM_DEPOSIT_NT;
+constexpr int gather_nt(int ext) { return ext <= 3 ? PM_GATHER_NT : PM_GATHER_NT_WIDE; }
 
 __device__ __forceinline__ int wrapi(int i, int N) { return i & (N - 1); }
 
@@ -83,18 +87,17 @@ struct Lane {
   int cx, cy, cz;              // central pixel (wrapped grid index)
   float wx[2 * EXT + 1], wy[2 * EXT + 1], wz[2 * EXT + 1];
   double S;                    // FP64 ball sum of the weights
+  double sx[EXT + 1];          // sum of wx over |dx| <= h
 };
 
 template <int EXT, int R2>
 __device__ __forceinline__ void lane_setup(Lane<EXT>& L, const KernelGeom& kg, float px, float py, float pz,
                                            bool with_sum) {
-  const double ux = (double)px * kg.inv_s, uy = (double)py * kg.inv_s, uz = (double)pz * kg.inv_s;
-  const double cxd = floor(ux + 0.5), cyd = floor(uy + 0.5), czd = floor(uz + 0.5);
   const int half = kg.N / 2;
-  L.cx = wrapi((int)cxd + half, kg.N);
-  L.cy = wrapi((int)cyd + half, kg.N);
-  L.cz = wrapi((int)czd + half, kg.N);
-  const float fx = (float)(cxd - ux), fy = (float)(cyd - uy), fz = (float)(czd - uz);
+  float fx, fy, fz;
+  L.cx = wrapi(central_pixel(px, kg.inv_s, &fx) + half, kg.N);
+  L.cy = wrapi(central_pixel(py, kg.inv_s, &fy) + half, kg.N);
+  L.cz = wrapi(central_pixel(pz, kg.inv_s, &fz) + half, kg.N);
 #pragma unroll
   for (int d = -EXT; d <= EXT; ++d) {
     const float ex = (float)d + fx, ey = (float)d + fy, ez = (float)d + fz;
@@ -103,18 +106,17 @@ __device__ __forceinline__ void lane_setup(Lane<EXT>& L, const KernelGeom& kg, f
     L.wz[d + EXT] = expf(-ez * ez * kg.inv2sig2);
   }
   L.S = 0.0;
-  if (!with_sum) return;
-  double sx[EXT + 1];
-  sx[0] = (double)L.wx[EXT];
+  L.sx[0] = (double)L.wx[EXT];
 #pragma unroll
-  for (int h = 1; h <= EXT; ++h) sx[h] = sx[h - 1] + ((double)L.wx[EXT - h] + (double)L.wx[EXT + h]);
+  for (int h = 1; h <= EXT; ++h) L.sx[h] = L.sx[h - 1] + ((double)L.wx[EXT - h] + (double)L.wx[EXT + h]);
+  if (!with_sum) return;
   double S = 0.0;
   static_for<-EXT, EXT + 1>([&](auto DZc) {
     constexpr int dz = decltype(DZc)::value;
     static_for<-EXT, EXT + 1>([&](auto DYc) {
       constexpr int dy = decltype(DYc)::value;
       constexpr int h = row_half(dy, dz, R2, EXT);
-      if constexpr (h >= 0) S += (double)L.wy[dy + EXT] * (double)L.wz[dz + EXT] * sx[h];
+      if constexpr (h >= 0) S += (double)L.wy[dy + EXT] * (double)L.wz[dz + EXT] * L.sx[h];
     });
   });
   L.S = S;
@@ -271,29 +273,6 @@ __global__ __launch_bounds__(kDepNT) void k_deposit_pieces(KernelGeom kg, const 
   }
 }
 
-// Tiles that may receive staged cells: those with a non-empty tile among their
-// 27 neighbours (periodic).  flag[t] = 1 or 0.
-__global__ __launch_bounds__(256) void k_mark_dest(const int* __restrict__ counts, int nt, int* flag) {
-  const int ntiles = nt * nt * nt;
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= ntiles) return;
-  const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
-  int any = 0;
-  for (int dz = -1; dz <= 1; ++dz)
-    for (int dy = -1; dy <= 1; ++dy)
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int u = ((((tz + dz) + nt) % nt) * nt + ((ty + dy) + nt) % nt) * nt + ((tx + dx) + nt) % nt;
-        any |= counts[u] > 0;
-      }
-  flag[t] = any;
-}
-
-__global__ __launch_bounds__(256) void k_compact(const int* __restrict__ flag, const int* __restrict__ off,
-                                                 int n, int* list) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t < n && flag[t]) list[off[t]] = t;
-}
-
 // Each listed tile: rho += the staged halo boxes of the pieces of its 27
 // neighbouring tiles, one cell per thread.  A neighbour's pieces are summed
 // exactly as integers (a lone piece read with the others' at once, 27
@@ -390,8 +369,211 @@ __global__ __launch_bounds__(kRedNT) void k_deposit_reduce(KernelGeom kg, const 
 // ---------------------------------------------------------------------------
 // gather + push
 // ---------------------------------------------------------------------------
+// A piece loads its tile plus a halo of EXT + 1 cells of phi into LDS once.
+// Its particles are then summed in one of two ways.
+//  - One particle per lane (balls with a compiled shape R2): the dilated ball
+//    is walked row by row (each wave takes every NW-th slice ez of the same 64
+//    particles, so that a piece's time falls with the block's waves), v_e = phi(c + e) - phi(c).  With S_h = sum_{|e| <= h}
+//    wx(e) v_e a row adds
+//       x:  wy wz (sum_e v_e (wx(e - 1) - wx(e + 1)))
+//       y:  wz (wy(ey - 1) S_{h(ey-1,ez)} - wy(ey + 1) S_{h(ey+1,ez)})
+//       z:  wy (wz(ez - 1) S_{h(ey,ez-1)} - wz(ez + 1) S_{h(ey,ez+1)})
+//    with w = 0 and h = -1 outside the ball: three FP32 instructions per cell
+//    (the subtraction and two multiply-adds) and some twenty per row, where
+//    products of three weights per cell take nine.
+//  - One particle per wave (the last few particles of a piece, and the other
+//    balls): lanes own the ball's rows (dy, dz) and step along dx together,
+//       x: phi(dx + 1) - phi(dx - 1), and the differences of the rows next to
+//    it in y and z, each times wx(dx); the rows are then summed over the wave.
+//    Four threads per particle have put its weights into LDS before.
+// A lane-per-particle pass over a compiled ball costs as much for one particle
+// as for 64, so the remainder of a piece goes by rows up to kRowMost particles
+// (the costs cross near 14 to 18 particles for the three compiled balls).
+// Bound: vector instructions at full waves, the serial length of a ball at few
+// particles.  65 537 particles of a mixture at sigma = 2 in a 256^3 box: a
+// smooth_accel call takes 134 us, 3000 us with one wave per particle reading
+// six neighbours per cell from memory; the ring (4097 particles, sigma = 1.5)
+// gathers and pushes in 40 us instead of 115 with a lane per particle alone.
+constexpr int kRowMost = 16;
+
+// Weights of up to NT / 4 particles (sorted order j0 ..) into w[p][3 W] (x, y, z),
+// four threads per particle, and their normalisations into norm[p].  base[p]:
+// the particle's central cell in the LDS tile (row pitch RP, plane pitch PP,
+// halo HE).  Ends with a barrier.
+template <int EXT, int NT>
+__device__ __forceinline__ void weights_to_lds(const KernelGeom& kg, const int* __restrict__ perm,
+                                               const float* __restrict__ pos, int j0, int count, int HE, int RP, int PP,
+                                               const int* hrow, float* w, double* norm, int* base, int* index) {
+  constexpr int W = 2 * EXT + 1, WS = 3 * W + 1;
+  const int p = threadIdx.x >> 2, q = threadIdx.x & 3;
+  const bool on = p < count;
+  float* wp = w + p * WS;
+  if (on) {
+    const int i = perm[j0 + p];
+    const int half = kg.N / 2;
+    float f[3];
+    int c[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      c[a] = wrapi(central_pixel(pos[3 * (int64_t)i + a], kg.inv_s, &f[a]) + half, kg.N) & (kTile - 1);
+    for (int d = q; d < 3 * W; d += 4) {
+      const int a = d / W;
+      const float e = (float)(d - a * W - EXT) + (a == 0 ? f[0] : a == 1 ? f[1] : f[2]);
+      wp[d] = expf(-e * e * kg.inv2sig2);
+    }
+    if (q == 0) {
+      base[p] = (c[2] + HE) * PP + (c[1] + HE) * RP + c[0] + HE;
+      index[p] = i;
+    }
+  }
+  __syncthreads();
+  double S = 0.0;
+  if (on && !kg.analytic) {
+    // sum over the ball, row by row: wy wz sum_{|dx| <= h} wx in FP64
+    double sx[EXT + 1];
+    sx[0] = (double)wp[EXT];
+#pragma unroll
+    for (int h = 1; h <= EXT; ++h) sx[h] = sx[h - 1] + ((double)wp[EXT - h] + (double)wp[EXT + h]);
+    for (int z = q; z < W; z += 4) {
+      double t = 0.0;
+      for (int y = 0; y < W; ++y) {
+        const int h = hrow[z * W + y];
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k <= EXT; ++k) v = (h == k) ? sx[k] : v;
+        t = fma((double)wp[W + y], v, t);
+      }
+      S = fma((double)wp[2 * W + z], t, S);
+    }
+  }
+  S += __shfl_xor(S, 1, 64);
+  S += __shfl_xor(S, 2, 64);
+  if (on && q == 0) norm[p] = kg.analytic ? kg.analytic_norm : S;
+  __syncthreads();
+}
+
+// Acceleration from the summed differences, then the store or the push.
+__device__ __forceinline__ void gather_out(const KernelGeom& kg, int64_t i, double norm, float gx, float gy, float gz,
+                                           float* pos, float* vel, float* acc, float dt_kick, float dt_drift,
+                                           int mode) {
+  const float f = (float)(-1.0 / (2.0 * (double)kg.s * norm));
+  const float ax = gx * f, ay = gy * f, az = gz * f;
+  if (mode == 0) {
+    acc[3 * i] = ax;
+    acc[3 * i + 1] = ay;
+    acc[3 * i + 2] = az;
+  } else {
+    const float vx = fmaf(ax, dt_kick, vel[3 * i]);
+    const float vy = fmaf(ay, dt_kick, vel[3 * i + 1]);
+    const float vz = fmaf(az, dt_kick, vel[3 * i + 2]);
+    vel[3 * i] = vx; vel[3 * i + 1] = vy; vel[3 * i + 2] = vz;
+    pos[3 * i] = fmaf(vx, dt_drift, pos[3 * i]);
+    pos[3 * i + 1] = fmaf(vy, dt_drift, pos[3 * i + 1]);
+    pos[3 * i + 2] = fmaf(vz, dt_drift, pos[3 * i + 2]);
+  }
+}
+
+// Sums the lane's particle over the dilated ball (compiled shape), base: its
+// central cell in the LDS tile: g = the three sums and the ball sum S of the
+// weights over the slices ez this wave owns (every NW-th).  The weights of the differences sum to zero
+// over the ball, so phi is taken relative to its value at the central pixel.
+// A row is summed in FP32 relative to its own middle cell, whose offset from
+// the centre enters with the row's weight sum in FP64, and the rows are added
+// in FP64: FP32 throughout loses two bits to the offsets that cancel between
+// rows (1.9e-7 against 5e-8 of the force at sigma = 2), this form none (8e-9).
+template <int EXT, int R2, int RP, int PP, int NW>
+__device__ __forceinline__ void lane_gather(const Lane<EXT>& L, const float* base, int wave, double* g) {
+  constexpr int HE = EXT + 1;
+  const float phc = base[0];
+  float wd[2 * EXT + 1];                          // wx(e - 1) - wx(e + 1), |e| < EXT
+#pragma unroll
+  for (int e = 1; e < 2 * EXT; ++e) wd[e] = L.wx[e - 1] - L.wx[e + 1];
+  double gx = 0.0, gy = 0.0, gz = 0.0, S = 0.0;
+  static_for<-HE, HE + 1>([&](auto EZc) {
+    constexpr int ez = decltype(EZc)::value;
+    if ((ez + HE) % NW != wave) return;
+    // weights of the slices ez, ez - 1 and ez + 1 (0 outside the ball)
+    const double wz = ez >= -EXT && ez <= EXT ? (double)L.wz[ez >= -EXT && ez <= EXT ? ez + EXT : 0] : 0.0;
+    const double wzm = ez - 1 >= -EXT ? (double)L.wz[ez - 1 >= -EXT ? ez - 1 + EXT : 0] : 0.0;
+    const double wzp = ez + 1 <= EXT ? (double)L.wz[ez + 1 <= EXT ? ez + 1 + EXT : 0] : 0.0;
+    double sx = 0.0, sy = 0.0, sw = 0.0;          // the slice's sums of x, y and the weights
+    static_for<-HE, HE + 1>([&](auto EYc) {
+      constexpr int ey = decltype(EYc)::value;
+      constexpr auto half = [](int y, int z) constexpr {
+        return y < -EXT || y > EXT || z < -EXT || z > EXT ? -1 : row_half(y, z, R2, EXT);
+      };
+      constexpr int h = half(ey, ez);
+      constexpr int hym = half(ey - 1, ez), hyp = half(ey + 1, ez), hzm = half(ey, ez - 1), hzp = half(ey, ez + 1);
+      constexpr int hy = hym > hyp ? hym : hyp, hz = hzm > hzp ? hzm : hzp;
+      constexpr int hs = hy > hz ? hy : hz;                     // cells the sums S need
+      constexpr int m = h >= 0 && h + 1 > hs ? h + 1 : hs;      // cells read
+      if constexpr (m >= 0) {
+        const float* row = base + ez * PP + ey * RP;
+        const float r0 = row[0];
+        float v[2 * m + 1];
+        v[m] = 0.0f;
+        static_for<1, m + 1>([&](auto Ec) {
+          constexpr int e = decltype(Ec)::value;
+          v[m - e] = row[-e] - r0;
+          v[m + e] = row[e] - r0;
+        });
+        if constexpr (h >= 0) {
+          float t = 0.0f;
+          static_for<-h - 1, h + 2>([&](auto Ec) {
+            constexpr int e = decltype(Ec)::value;
+            // wx(e - 1) and wx(e + 1) where they lie in the row
+            if constexpr (e == 0) {}
+            else if constexpr (e - 1 >= -h && e + 1 <= h) t = fmaf(v[e + m], wd[e + EXT], t);
+            else if constexpr (e - 1 >= -h && e - 1 <= h) t = fmaf(v[e + m], L.wx[e - 1 + EXT], t);
+            else if constexpr (e + 1 >= -h && e + 1 <= h) t = fmaf(v[e + m], -L.wx[e + 1 + EXT], t);
+          });
+          sx = fma((double)t, (double)L.wy[h >= 0 ? ey + EXT : 0], sx);
+          sw = fma((double)L.wy[h >= 0 ? ey + EXT : 0], L.sx[h >= 0 ? h : 0], sw);
+        }
+        if constexpr (hs >= 0) {
+          float s[hs + 1];
+          s[0] = 0.0f;
+          static_for<1, hs + 1>([&](auto Ec) {
+            constexpr int e = decltype(Ec)::value;
+            s[e] = fmaf(v[m - e], L.wx[EXT - e], fmaf(v[m + e], L.wx[EXT + e], s[e - 1]));
+          });
+          const double off = (double)(r0 - phc);
+          auto Sh = [&](auto Hc) {
+            constexpr int k = decltype(Hc)::value;
+            return fma(off, L.sx[k], (double)s[k]);
+          };
+          if constexpr (hym >= 0) sy = fma((double)L.wy[hym >= 0 ? ey - 1 + EXT : 0], Sh(std::integral_constant<int, hym >= 0 ? hym : 0>{}), sy);
+          if constexpr (hyp >= 0) sy = fma(-(double)L.wy[hyp >= 0 ? ey + 1 + EXT : 0], Sh(std::integral_constant<int, hyp >= 0 ? hyp : 0>{}), sy);
+          if constexpr (hz >= 0) {
+            double t = 0.0;
+            if constexpr (hzm >= 0) t = wzm * Sh(std::integral_constant<int, hzm >= 0 ? hzm : 0>{});
+            if constexpr (hzp >= 0) t = fma(-wzp, Sh(std::integral_constant<int, hzp >= 0 ? hzp : 0>{}), t);
+            gz = fma(t, (double)L.wy[hz >= 0 ? ey + EXT : 0], gz);
+          }
+        }
+      }
+    });
+    gx = fma(sx, wz, gx);
+    gy = fma(sy, wz, gy);
+    S = fma(sw, wz, S);
+  });
+  g[0] = gx;
+  g[1] = gy;
+  g[2] = gz;
+  g[3] = S;
+}
+
+// Floats of LDS before the tile: the lane pass's sums or the row pass's weights.
+template <int EXT>
+constexpr int gather_scratch() {
+  constexpr int nt = gather_nt(EXT);
+  constexpr int a = nt / 64 * 4 * 64 * 2, b = nt / 4 * (3 * (2 * EXT + 1) + 1);
+  return (a > b ? a : b) + 1 & ~1;
+}
+
+// R2 = 0: a ball without a compiled shape, all particles by rows.
 template <int EXT, int R2>
-__global__ __launch_bounds__(kGatNT) void k_gather_pieces(KernelGeom kg, const int* __restrict__ perm,
+__global__ __launch_bounds__(gather_nt(EXT)) void k_gather_pieces(KernelGeom kg, const int* __restrict__ perm,
                                                        const int* __restrict__ offsets,
                                                        const int* __restrict__ pc_off,
                                                        const int* __restrict__ ptile, int ntiles, int piece,
@@ -401,105 +583,112 @@ __global__ __launch_bounds__(kGatNT) void k_gather_pieces(KernelGeom kg, const i
   constexpr int HE = EXT + 1;                      // ball plus the difference stencil
   constexpr int TE = kTile + 2 * HE;
   constexpr int RP = TE + 1, PP = RP * TE + 1;     // padded row and plane pitches
-  extern __shared__ float tile[];
+  constexpr int W = 2 * EXT + 1, WS = 3 * W + 1;
+  constexpr int RU = (W * W + 63) / 64;            // rows per lane, at most
+  constexpr int kGatNT = gather_nt(EXT), NW = kGatNT / 64;
+  constexpr int kRowBatch = kGatNT / 4;            // particles whose weights LDS holds at once
+  extern __shared__ double gsm[];
+  double* red = gsm;                               // [NW][4][64] sums of the lane pass, or
+  float* wbuf = reinterpret_cast<float*>(gsm);     // [kRowBatch][WS] weights of the row pass
+  float* tile = reinterpret_cast<float*>(gsm) + gather_scratch<EXT>();
+  __shared__ double norm[kRowBatch];
+  __shared__ int cell[kRowBatch], index[kRowBatch];
+  __shared__ int hrow[W * W];
+  __shared__ int slot;
   const int N = kg.N, nt = N / kTile;
   const int total = pc_off[ntiles];
-  __shared__ int slot;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int j = threadIdx.x; j < W * W; j += kGatNT) hrow[j] = -1;
+  __syncthreads();
+  for (int j = threadIdx.x; j < kg.nrows; j += kGatNT) {
+    const int r = kg.rows[j];
+    hrow[(((r >> 8) & 255) - 16 + EXT) * W + (r & 255) - 16 + EXT] = r >> 16;
+  }
+  int roff[RU], rh[RU], ry[RU], rz[RU];
+#pragma unroll
+  for (int u = 0; u < RU; ++u) {
+    const int k = lane + 64 * u;
+    const int r = k < kg.nrows ? kg.rows[k] : (16 | 16 << 8);
+    ry[u] = (r & 255) - 16;
+    rz[u] = ((r >> 8) & 255) - 16;
+    rh[u] = k < kg.nrows ? r >> 16 : -1;
+    roff[u] = rz[u] * PP + ry[u] * RP;
+  }
   for (int p = next_piece(counter, &slot); p < total; p = next_piece(counter, &slot)) {
     const int t = ptile[p];
     const int a = offsets[t] + (p - pc_off[t]) * piece;
     const int b = min(a + piece, offsets[t + 1]);
     const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
     const int ox = tx * kTile - HE, oy = ty * kTile - HE, oz = tz * kTile - HE;
+#pragma unroll 8
     for (int j = threadIdx.x; j < TE * TE * TE; j += kGatNT) {
       const int lx = j % TE, ly = (j / TE) % TE, lz = j / (TE * TE);
       tile[lz * PP + ly * RP + lx] =
           phi[((long long)wrapi(oz + lz, N) * N + wrapi(oy + ly, N)) * N + wrapi(ox + lx, N)];
     }
     __syncthreads();
-    for (int j = a + (int)threadIdx.x; j < b; j += kGatNT) {
-      const int64_t i = perm[j];
-      const float x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
-      Lane<EXT> L;
-      lane_setup<EXT, R2>(L, kg, x, y, z, !kg.analytic);
-      const double norm = kg.analytic ? kg.analytic_norm : L.S;
-      const int lx = wrapi(L.cx - ox, N), ly = wrapi(L.cy - oy, N), lz = wrapi(L.cz - oz, N);
-      const float* base = tile + (lz - HE) * PP + (ly - HE) * RP + (lx - HE);
-      // The folded weights sum to zero over the dilated ball, so phi can be
-      // taken relative to its value at the central pixel: the products then
-      // carry the small differences, not the potential's offset (in FP32 the
-      // offset would cost up to a hundred times the rounding error).
-      const float phc = base[HE * PP + HE * RP + HE];
-      float gx = 0.f, gy = 0.f, gz = 0.f;
-      static_for<-HE, HE + 1>([&](auto EZc) {
-        constexpr int ez = decltype(EZc)::value;
-        static_for<-HE, HE + 1>([&](auto EYc) {
-          constexpr int ey = decltype(EYc)::value;
-          static_for<-HE, HE + 1>([&](auto EXc) {
-            constexpr int ex = decltype(EXc)::value;
-            constexpr bool bxm = in_ball(ex - 1, ey, ez, R2, EXT), bxp = in_ball(ex + 1, ey, ez, R2, EXT);
-            constexpr bool bym = in_ball(ex, ey - 1, ez, R2, EXT), byp = in_ball(ex, ey + 1, ez, R2, EXT);
-            constexpr bool bzm = in_ball(ex, ey, ez - 1, R2, EXT), bzp = in_ball(ex, ey, ez + 1, R2, EXT);
-            if constexpr (bxm || bxp || bym || byp || bzm || bzp) {
-              constexpr int off = (ez + HE) * PP + (ey + HE) * RP + (ex + HE);
-              const float v = base[off] - phc;
-              // W_x(e) = w(e - e_x) - w(e + e_x), and likewise for y and z
-              if constexpr (bxm || bxp) {
-                float wdx = 0.f;
-                if constexpr (bxm) wdx += L.wx[ex - 1 + EXT];
-                if constexpr (bxp) wdx -= L.wx[ex + 1 + EXT];
-                gx = fmaf(v * wdx, L.wy[ey + EXT] * L.wz[ez + EXT], gx);
-              }
-              if constexpr (bym || byp) {
-                float wdy = 0.f;
-                if constexpr (bym) wdy += L.wy[ey - 1 + EXT];
-                if constexpr (byp) wdy -= L.wy[ey + 1 + EXT];
-                gy = fmaf(v * wdy, L.wx[ex + EXT] * L.wz[ez + EXT], gy);
-              }
-              if constexpr (bzm || bzp) {
-                float wdz = 0.f;
-                if constexpr (bzm) wdz += L.wz[ez - 1 + EXT];
-                if constexpr (bzp) wdz -= L.wz[ez + 1 + EXT];
-                gz = fmaf(v * wdz, L.wx[ex + EXT] * L.wy[ey + EXT], gz);
-              }
-            }
-          });
-        });
-      });
-      // sum_e phi(c + e) W(e) = sum_d w(d) (phi(c + d + e_x) - phi(c + d - e_x)),
-      // so the smoothed force is -1 / (2 s S) times it
-      const float f = (float)(-1.0 / (2.0 * (double)kg.s * norm));
-      const float ax = gx * f, ay = gy * f, az = gz * f;
-      if (mode == 0) {
-        acc[3 * i] = ax;
-        acc[3 * i + 1] = ay;
-        acc[3 * i + 2] = az;
-      } else {
-        const float vx = fmaf(ax, dt_kick, vel[3 * i]);
-        const float vy = fmaf(ay, dt_kick, vel[3 * i + 1]);
-        const float vz = fmaf(az, dt_kick, vel[3 * i + 2]);
-        vel[3 * i] = vx; vel[3 * i + 1] = vy; vel[3 * i + 2] = vz;
-        pos[3 * i] = fmaf(vx, dt_drift, x);
-        pos[3 * i + 1] = fmaf(vy, dt_drift, y);
-        pos[3 * i + 2] = fmaf(vz, dt_drift, z);
+    const int tail = (b - a) & 63;
+    const int mid = R2 == 0 ? a : (tail > kRowMost ? b : b - tail);
+    if constexpr (R2 > 0) {
+      // 64 particles at a time, one per lane, the ball's slices dealt to the waves
+      for (int j0 = a; j0 < mid; j0 += 64) {
+        const int64_t i = perm[min(j0 + lane, mid - 1)];
+        Lane<EXT> L;
+        lane_setup<EXT, R2>(L, kg, pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], false);
+        const int lx = (L.cx & (kTile - 1)) + HE, ly = (L.cy & (kTile - 1)) + HE, lz = (L.cz & (kTile - 1)) + HE;
+        double g[4];
+        lane_gather<EXT, R2, RP, PP, NW>(L, tile + lz * PP + ly * RP + lx, wave, g);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) red[(wave * 4 + c) * 64 + lane] = g[c];
+        __syncthreads();
+        if (wave == 0 && j0 + lane < mid) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            for (int w = 1; w < NW; ++w) g[c] += red[(w * 4 + c) * 64 + lane];
+          gather_out(kg, i, kg.analytic ? kg.analytic_norm : g[3], (float)g[0], (float)g[1], (float)g[2], pos, vel, acc,
+                     dt_kick, dt_drift, mode);
+        }
+        __syncthreads();
       }
     }
-    __syncthreads();
+    for (int j0 = mid; j0 < b; j0 += kRowBatch) {
+      const int count = min(kRowBatch, b - j0);
+      weights_to_lds<EXT, kGatNT>(kg, perm, pos, j0, count, HE, RP, PP, hrow, wbuf, norm, cell, index);
+      for (int k = wave; k < count; k += kGatNT / 64) {
+        const float* wp = wbuf + k * WS;
+        const float* c0 = tile + cell[k];
+        float gx = 0.0f, gy = 0.0f, gz = 0.0f;
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+          if (64 * u >= kg.nrows) break;
+          const float* r = c0 + roff[u];
+          float sx = 0.0f, sy = 0.0f, sz = 0.0f;
+          float vm = r[-EXT - 1], v0 = r[-EXT];
+#pragma unroll
+          for (int dx = -EXT; dx <= EXT; ++dx) {
+            const float vp = r[dx + 1];
+            const float w = (dx < 0 ? -dx : dx) <= rh[u] ? wp[dx + EXT] : 0.0f;
+            sx = fmaf(w, vp - vm, sx);
+            sy = fmaf(w, r[dx + RP] - r[dx - RP], sy);
+            sz = fmaf(w, r[dx + PP] - r[dx - PP], sz);
+            vm = v0;
+            v0 = vp;
+          }
+          const float wyz = wp[W + ry[u] + EXT] * wp[2 * W + rz[u] + EXT];
+          gx = fmaf(wyz, sx, gx);
+          gy = fmaf(wyz, sy, gy);
+          gz = fmaf(wyz, sz, gz);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+          gx += __shfl_xor(gx, o, 64);
+          gy += __shfl_xor(gy, o, 64);
+          gz += __shfl_xor(gz, o, 64);
+        }
+        if (lane == 0) gather_out(kg, index[k], norm[k], gx, gy, gz, pos, vel, acc, dt_kick, dt_drift, mode);
+      }
+      __syncthreads();
+    }
   }
-}
-
-// The tile of every piece: ptile[q] = t for pc_off[t] <= q < pc_off[t + 1].
-__global__ __launch_bounds__(256) void k_piece_tiles(const int* __restrict__ pc_off, int n, int* ptile) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= n) return;
-  for (int q = pc_off[t]; q < pc_off[t + 1]; ++q) ptile[q] = t;
-}
-
-// Pieces per tile: ceil(count / piece).
-__global__ __launch_bounds__(256) void k_piece_counts(const int* __restrict__ counts, int n, int piece,
-                                                      int* pieces) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t < n) pieces[t] = (counts[t] + piece - 1) / piece;
 }
 
 // Grid sizes of the persistent kernels.
@@ -513,7 +702,7 @@ static constexpr size_t deposit_lds() {
 template <int EXT>
 static constexpr size_t gather_lds() {
   constexpr int TE = kTile + 2 * (EXT + 1);
-  return sizeof(float) * (size_t)TE * ((TE + 1) * TE + 1);
+  return sizeof(float) * ((size_t)TE * ((TE + 1) * TE + 1) + gather_scratch<EXT>());
 }
 
 size_t piece_stage_cells(int ext, int cap) {
@@ -521,37 +710,19 @@ size_t piece_stage_cells(int ext, int cap) {
   return (size_t)cap * te * te * te;
 }
 
-hipError_t piece_plan(const PieceBufs& pb, const SortBufs& sb, int N, hipStream_t st) {
-  const int ntiles = sb.ntiles;
-  // pieces per tile, their offsets, then the tiles that receive staged cells
-  hipLaunchKernelGGL(k_piece_counts, dim3((ntiles + 255) / 256), dim3(256), 0, st, sb.counts, ntiles, kPiece,
-                     pb.flag);
-  hipError_t e = scan_exclusive(pb.flag, ntiles, pb.pc_off, sb.blocksums, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_piece_tiles, dim3((ntiles + 255) / 256), dim3(256), 0, st, pb.pc_off, ntiles, pb.ptile);
-  const int nt = N / kTile;
-  hipLaunchKernelGGL(k_mark_dest, dim3((ntiles + 255) / 256), dim3(256), 0, st, sb.counts, nt, pb.flag);
-  if ((e = scan_exclusive(pb.flag, ntiles, pb.list_off, sb.blocksums, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_compact, dim3((ntiles + 255) / 256), dim3(256), 0, st, pb.flag, pb.list_off, ntiles,
-                     pb.list);
-  return hipGetLastError();
-}
-
 hipError_t deposit_pieces(const KernelGeom& kg, const SortBufs& sb, const PieceBufs& pb, const float* pos,
                           const float* mass, int64_t n, float* rho, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipError_t e = fill_zero(reinterpret_cast<float*>(pb.counter), 1, st);
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
   const int nt = kg.N / kTile;
   // the tiles' fixed-point scales: their largest |m|
-  if ((e = fill_zero(reinterpret_cast<float*>(pb.tmax), sb.ntiles, st)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_tile_mass_max, dim3(kPersistBlocks), dim3(kNT), 0, st, sb.perm, sb.offsets, pb.pc_off, pb.ptile,
-                     sb.ntiles, kPiece, mass, pb.tmax);
+                     sb.ntiles, kg.piece, mass, pb.tmax);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   switch (kg.piece_ext) {
     case 3:
       hipLaunchKernelGGL((k_deposit_pieces<3, 16>), dim3(kPersistBlocks), dim3(kDepNT), deposit_lds<3>(), st, kg,
-                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kPiece, pb.counter, pos, mass, pb.tmax,
+                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kg.piece, pb.counter, pos, mass, pb.tmax,
                          pb.stage, pb.cap, rho);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       hipLaunchKernelGGL((k_deposit_reduce<3>), dim3(kPersistBlocks), dim3(kRedNT), 0, st, kg, pb.list,
@@ -560,7 +731,7 @@ hipError_t deposit_pieces(const KernelGeom& kg, const SortBufs& sb, const PieceB
       break;
     case 5:
       hipLaunchKernelGGL((k_deposit_pieces<5, 36>), dim3(kPersistBlocks), dim3(kDepNT), deposit_lds<5>(), st, kg,
-                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kPiece, pb.counter, pos, mass, pb.tmax,
+                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kg.piece, pb.counter, pos, mass, pb.tmax,
                          pb.stage, pb.cap, rho);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       hipLaunchKernelGGL((k_deposit_reduce<5>), dim3(kPersistBlocks), dim3(kRedNT), 0, st, kg, pb.list,
@@ -577,22 +748,22 @@ hipError_t gather_pieces(const KernelGeom& kg, const SortBufs& sb, const PieceBu
                          float* pos, float* vel, float* acc, int64_t n, float dt_kick, float dt_drift, int mode,
                          hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipError_t e = fill_zero(reinterpret_cast<float*>(pb.counter + 1), 1, st);
-  if (e != hipSuccess) return e;
-  switch (kg.piece_ext) {
-    case 3:
-      hipLaunchKernelGGL((k_gather_pieces<3, 16>), dim3(kPersistBlocks), dim3(kGatNT), gather_lds<3>(), st, kg,
-                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kPiece, pb.counter + 1, phi, pos, vel, acc,
-                         dt_kick, dt_drift, mode);
-      break;
-    case 5:
-      hipLaunchKernelGGL((k_gather_pieces<5, 36>), dim3(kPersistBlocks), dim3(kGatNT), gather_lds<5>(), st, kg,
-                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kPiece, pb.counter + 1, phi, pos, vel, acc,
-                         dt_kick, dt_drift, mode);
-      break;
-    default:
-      return hipErrorInvalidValue;
+#define GATHER(EXT, R2)                                                                                            \
+  hipLaunchKernelGGL((k_gather_pieces<EXT, R2>), dim3(kPersistBlocks), dim3(gather_nt(EXT)), gather_lds<EXT>(), st, kg,    \
+                     sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kg.piece, pb.counter + 1, phi, pos, vel, \
+                     acc, dt_kick, dt_drift, mode)
+  switch (kg.plan_ext) {
+    case 1: GATHER(1, 0); break;
+    case 2: GATHER(2, 0); break;
+    case 3: if (kg.nball == 251) GATHER(3, 16); else GATHER(3, 0); break;
+    case 4: GATHER(4, 0); break;
+    case 5: if (kg.nball == 895) GATHER(5, 36); else GATHER(5, 0); break;
+    case 6: GATHER(6, 0); break;
+    case 7: if (kg.nball == 2103) GATHER(7, 64); else GATHER(7, 0); break;
+    case 8: GATHER(8, 0); break;
+    default: return hipErrorInvalidValue;
   }
+#undef GATHER
   return hipGetLastError();
 }
 

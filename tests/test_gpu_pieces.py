@@ -1,0 +1,60 @@
+"""Tile-piece gather and deposit over the kernel balls they take and at the
+edges of their work split (waves of 64, the row remainder, several pieces),
+against the FP64 oracle on the same FP32 inputs."""
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.gpu_util import dev, host, oparams, rel_max
+from oracle import pm as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    from paper_2312_02968_amd import mondpm
+    return mondpm
+
+
+def _clump(seed, n, count, sigma, n_pad=None):
+    """count particles inside one 8^3 tile and a few far ones (one per tile)."""
+    rng = np.random.default_rng(seed)
+    pos = np.concatenate([rng.uniform(-0.4, 7.4, (count, 3)), rng.uniform(-n / 4, n / 4, (5, 3))])
+    mass = rng.uniform(0.2, 2.0, len(pos))
+    p = W.params(n, n_pad=n_pad, sigma=sigma)
+    return p, pos.astype(np.float32), mass.astype(np.float32)
+
+
+# Both sides start from the same FP32 potential: each force is a sum of FP32
+# differences with FP32 weights (one rounding each), so 16 roundings of the
+# largest force bound it.
+@pytest.mark.parametrize("sigma", [0.5, 0.75, 1.0, 1.25, 1.5, 1.75, 2.0, 2.25])
+@pytest.mark.parametrize("count", [1, 16, 17, 64, 65, 129, 300])
+def test_gather_balls_and_remainders(M, sigma, count):
+    print("gather", sigma, count, flush=True)
+    p, pos, mass = _clump(count, 32, count, sigma)
+    op = oparams(p)
+    phi = np.random.default_rng(1).standard_normal((4, 4, 4))
+    phi = np.kron(phi, np.ones((16, 16, 16)))                   # smooth by three box filters
+    for ax in range(3):
+        phi = sum(np.roll(phi, s, ax) for s in range(-8, 8)) / 16
+    phi32 = (phi + 3.0).astype(np.float32)
+    ctx = M.pm_create(p, len(pos))
+    acc = dev(np.zeros_like(pos))
+    M.smooth_accel(ctx, dev(phi32.ravel()), dev(pos), acc)
+    ref = orc.smooth_accel(op, phi32.astype(np.float64), pos.astype(np.float64))
+    assert rel_max(host(acc), ref) < 1e-6
+    ctx.close()
+
+
+def test_gather_smallest_box_with_a_wide_ball(M):
+    """A 16^3 box is two tiles across: the halo of the widest ball wraps around it."""
+    p, pos, mass = _clump(3, 8, 70, 2.25, n_pad=16)
+    phi32 = np.random.default_rng(2).standard_normal((16, 16, 16)).astype(np.float32)
+    ctx = M.pm_create(p, len(pos))
+    acc = dev(np.zeros_like(pos))
+    M.smooth_accel(ctx, dev(phi32.ravel()), dev(pos), acc)
+    ref = orc.smooth_accel(oparams(p), phi32.astype(np.float64), pos.astype(np.float64))
+    assert rel_max(host(acc), ref) < 1e-6
+    ctx.close()
