@@ -36,8 +36,26 @@ def _sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
-def _compile(src, defines=(), build_dir=BUILD):
-    obj = os.path.join(build_dir, os.path.basename(src) + ".o")
+# pm_fft.hip is compiled once per box size (and once for the rest, part 0):
+# its instantiations take minutes in one translation unit
+FFT_PARTS = (1024, 512, 256, 128, 64, 32, 16, 0)
+
+
+def _jobs():
+    jobs = []
+    for src in _sources():
+        if os.path.basename(src) == "pm_fft.hip":
+            jobs = [(src, n) for n in FFT_PARTS] + jobs
+        else:
+            jobs.append((src, None))
+    return jobs
+
+
+def _compile(src, part=None, defines=(), build_dir=BUILD):
+    tag = "" if part is None else f".{part}"
+    obj = os.path.join(build_dir, os.path.basename(src) + tag + ".o")
+    if part is not None:
+        defines = (*defines, f"PM_FFT_PART={part}")
     cmd = [HIPCC, *COMMON, *[f"-D{d}" for d in defines], "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -48,9 +66,8 @@ def _compile(src, defines=(), build_dir=BUILD):
 def build(verbose=False, defines=(), lib=LIB, build_dir=BUILD) -> str:
     """Compile and link; defines (NAME=VALUE) set compile-time launch shapes."""
     os.makedirs(build_dir, exist_ok=True)
-    srcs = _sources()
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(lambda s: _compile(s, defines, build_dir), srcs))
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(lambda j: _compile(j[0], j[1], defines, build_dir), _jobs()))
     tmp = lib + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

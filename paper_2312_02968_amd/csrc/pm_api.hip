@@ -114,6 +114,13 @@ static int timer_of(PassKind k) {
     case PASS_X_MU: return PM_T_X_MU;
     case PASS_Y_FWD: return PM_T_Y_FWD;
     case PASS_Y_INV: return PM_T_Y_INV;
+    case PASS_Y_DOT: return PM_T_Y_FWD;
+    case PASS_Y_GRAD: return PM_T_Y_INV;
+    case PASS_Y_GRAD_ADD: return PM_T_Y_INV;
+    case PASS_P_NEWTON: return PM_T_Z_NEWTON;
+    case PASS_P_CURL: return PM_T_Z_CURL;
+    case PASS_P_FINAL: return PM_T_Z_CURL_FINAL;
+    case PASS_P_DIV: return PM_T_Z_DIV;
     case PASS_Z_FWD: return PM_T_Z_FWD;
     case PASS_Z_INV: return PM_T_Z_INV;
     case PASS_Z_NEWTON: return PM_T_Z_NEWTON;
@@ -238,8 +245,10 @@ static size_t carve(pm_ctx* c, Carver& cv) {
   const size_t nb = (ntiles + 1023) / 1024;
   c->spec = cv.take<float2>(3 * C);
   c->phiN = cv.take<float2>(C);
-  c->rho = cv.take<float>(R);
-  c->phi = cv.take<float>(R);
+  // the internal grids also hold the potential form's pair during a solve
+  // (a one-component spectrum is a little larger than a grid)
+  c->rho = cv.take<float>(R > 2 * C ? R : 2 * C);
+  c->phi = cv.take<float>(R > 2 * C ? R : 2 * C);
   c->fprev = (need_residual(c->p) || (c->p.flags & PM_F_WARM_START)) ? cv.take<float>(3 * R) : nullptr;
   c->scales = cv.take<float>(scale_floats((int)N, c->P));
   c->ctl = cv.take<int>(16);
@@ -449,6 +458,27 @@ static ZArgs zargs(pm_ctx* c) {
   return z;
 }
 
+// A pass in potential form on the pair (a, b) and the field in c->spec.
+static PassDesc ppdesc(pm_ctx* c, PassKind k, float2* a, float2* b, const float* kd, Gate gate) {
+  PassDesc d;
+  d.kind = k;
+  d.gate = gate;
+  const double N = c->N;
+  d.p.f = c->spec;
+  d.p.a = a;
+  d.p.b = b;
+  d.p.phiN = c->phiN;
+  d.p.kv = c->kv;
+  d.p.kt = c->kt;
+  d.p.kap = c->kap;
+  d.p.kd = kd;
+  d.p.newton_coef = (float)(-4.0 * M_PI * c->p.G);
+  d.p.scale = (float)(1.0 / (N * N * N));
+  d.p.fscale = (float)(1.0 / N);
+  d.p.partials = c->partials;
+  return d;
+}
+
 // The increment form of the solve (Sect. 5, item (v)): the density, the
 // Newton field and H are increments, Eqs. inverse and interpolation are
 // linearised about F and g_M of the previous solve, and the spectra between
@@ -550,7 +580,20 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
     d.gate = run0;
     return d;
   };
-  {
+  // The potential form (pm_fft.hip) serves every solve with FP32 spectra and
+  // FP32 transforms; FP16 spectra keep the component form their scales belong
+  // to, and so does the matrix-core policy, whose y passes have no pair form.
+  const bool pot = !io && !c->fg.bf16x3;
+  float2* s0 = c->spec;
+  float2* s1 = c->spec + c->fg.comp_stride;
+  float2* w0 = reinterpret_cast<float2*>(c->rho);
+  float2* w1 = reinterpret_cast<float2*>(c->phi);
+  auto ppass = [&](PassKind k, float2* a, float2* b, Gate gate) { return pass(c, ppdesc(c, k, a, b, c->kt, gate)); };
+  if (pot && !start && !learned) {
+    HIPCHK(pass(c, ppdesc(c, PASS_P_NEWTON, s0, s1, c->kap, Gate{})));
+    HIPCHK(reduce_partials(c->partials, zpot_blocks(N), c->dacc, c->st));
+    HIPCHK(pass(c, ppdesc(c, PASS_Y_GRAD, s0, s1, c->kap, run0)));
+  } else {
     PassDesc d = pdesc(PASS_Z_NEWTON, c->spec);
     d.z = zargs(c);
     d.z.with_h0 = warm ? 2 : (coarse ? 3 : ((start || learned) ? 1 : 0));
@@ -582,7 +625,9 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
     if (resid && k >= 2) HIPCHK(reduce_partials(c->partials, x_blocks(N), c->dacc + (k - 1), c->st, run0));
     if (dev_tol) HIPCHK(tol_check(c->ctl, c->dacc, k, K, p.tol, N3, c->st));
     k_done = k;
-    {
+    if (pot) {
+      HIPCHK(ppass(PASS_Y_DOT, s0, s1, run01));
+    } else {
       PassDesc d = spec3(PASS_Y_FWD);
       d.gate = run01;
       HIPCHK(pass(c, d));
@@ -590,22 +635,28 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
     if (dev_tol || k == K) {
       // the last projection, to phi: in the tolerance mode enqueued every
       // iteration and run by the one in which the iteration stops
-      PassDesc d = pdesc(PASS_Z_CURL_FINAL, c->spec);
-      d.z = zargs(c);
-      d.io = io ? 3 : 0;
-      d.z.out = fin;
-      d.gate = run1;
+      PassDesc d = ppdesc(c, PASS_P_FINAL, s0, s1, c->kt, run1);
+      if (!pot) {
+        d = pdesc(PASS_Z_CURL_FINAL, c->spec);
+        d.z = zargs(c);
+        d.io = io ? 3 : 0;
+        d.z.out = fin;
+        d.gate = run1;
+      }
       HIPCHK(pass(c, d));
       if (!dev_tol) break;
       HIPCHK(gate_advance(c->ctl, c->st));
       if (k == K) break;
     }
-    {
+    if (pot) {
+      HIPCHK(ppass(PASS_P_CURL, s0, s1, run0));
+      HIPCHK(ppass(PASS_Y_GRAD, s0, s1, run0));
+    } else {
       PassDesc d = spec3(PASS_Z_CURL);
       d.z = zargs(c);
       HIPCHK(pass(c, d));
+      HIPCHK(pass(c, spec3(PASS_Y_INV)));
     }
-    HIPCHK(pass(c, spec3(PASS_Y_INV)));
     {
       PassDesc d = spec3(inc ? PASS_X_LIN_MU : PASS_X_MU);
       d.mu_mode = p.mu;
@@ -613,13 +664,17 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
       d.base = inc ? inc->gM : nullptr;
       HIPCHK(pass(c, d));
     }
-    HIPCHK(pass(c, spec3(PASS_Y_FWD)));
-    {
+    if (pot) {
+      HIPCHK(ppass(PASS_Y_DOT, w0, w1, run0));
+      HIPCHK(ppass(PASS_P_DIV, w0, w1, run0));
+      HIPCHK(ppass(PASS_Y_GRAD_ADD, w0, w1, run0));
+    } else {
+      HIPCHK(pass(c, spec3(PASS_Y_FWD)));
       PassDesc d = spec3(PASS_Z_DIV);
       d.z = zargs(c);
       HIPCHK(pass(c, d));
+      HIPCHK(pass(c, spec3(PASS_Y_INV)));
     }
-    HIPCHK(pass(c, spec3(PASS_Y_INV)));
   }
   if (inc) {
     // fprev now holds an increment, not a field a warm start could use

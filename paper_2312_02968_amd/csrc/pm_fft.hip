@@ -1438,30 +1438,305 @@ __global__ __launch_bounds__(NT) void k_zpass(ZArgs a, const float2* __restrict_
   store_cols<L, T, NT, First::R, HZ * NOUT, CS>(v, E, dst, nvs, row);
 }
 
-// Sum of partials[0..n) into out[0] (FP64), one block.
-__global__ __launch_bounds__(1024) void k_reduce_partials(const double* __restrict__ partials, int n,
-                                                          double* out, Gate gate) {
-  if (gated_off(gate)) return;
-  __shared__ double red[16];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < n; i += 1024) acc += partials[i];
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int w = 0; w < 16; ++w) t += red[w];
-    out[0] = t;
+// ----------------------------------------------------------------------------
+// Potential form of the curl-free and divergence-free projections.
+//
+// Both projections act on one scalar per mode.  With kt the projections'
+// wavevector, the curl-free part of g is kt psi with psi = At (kt . g), and the
+// divergence-free step is F = F' + kt psi with psi = At kt . (g_N - F').  The
+// scalar product splits by axis: A = ktx gx + kty gy is known after the y
+// transform and B = gz adds ktz gz after the z transform, so the forward y
+// pass (Y_DOT) reads three components and writes the pair (A, B); the z pass
+// transforms two spectra each way instead of three and writes the pair
+// (invz psi, invz (ktz psi)); and the inverse y pass (Y_GRAD) makes the three
+// components of kt psi again, ktx invy(p), invy(kty p) and invy(q).  The
+// Newton field -i kappa phi_N has the same form with kappa in place of kt.
+// For the divergence-free step the x pass's output F'(kx, y, z) stays where it
+// is and Y_GRAD_ADD adds the correction to it, so F' takes no part in the y and
+// z transforms' rounding.  Bytes per half iteration in spectra of one
+// component: curl-free 5 + 4 + 5 (18 in components), divergence-free
+// 5 + 5 + 8 (19), and four z transforms per column instead of six.
+// ----------------------------------------------------------------------------
+#ifndef PM_NTYP
+#define PM_NTYP 1024
+#endif
+#ifndef PM_YP_WAVES
+#define PM_YP_WAVES 1
+#endif
+#ifndef PM_TY512
+#define PM_TY512 16
+#endif
+#ifndef PM_TY1024
+#define PM_TY1024 8
+#endif
+#ifndef PM_NTY1024
+#define PM_NTY1024 1024
+#endif
+#ifndef PM_NTZ1024
+#define PM_NTZ1024 1024
+#endif
+#ifndef PM_TZ1024
+#define PM_TZ1024 16
+#endif
+#ifndef PM_TZP
+#define PM_TZP 8
+#endif
+#ifndef PM_NTZP
+#define PM_NTZP 512
+#endif
+// Columns and threads of the passes in potential form, measured at 512^3 and
+// 1024^3 (ms per K = 4 solve).  y: 16 columns (whole 128-byte lines) with 1024
+// threads at 512 (20.4; 512 threads 20.4, 8 columns 20.9); at 1024 the registers
+// of 16 columns spill (212) and 8 are taken (195; with 512 threads 198).  z: 8
+// columns with 512 threads at 512 (16 columns 20.6 to 20.8 against 20.3); at
+// 1024 16 columns with 1024 threads (193 against 195).  Below, as many threads
+// as a radix stage has butterflies, so that no wave of a block idles (the
+// plans of 64 to 256 points have 8 to 16 butterflies per column).
+template <int L>
+struct PCfg {
+  static constexpr int TY = L == 1024 ? PM_TY1024 : L == 512 ? PM_TY512 : 16;
+  static constexpr int NTY = L == 1024 ? PM_NTY1024 : L == 512 ? PM_NTYP : L >= 128 ? 256 : 128;
+  static constexpr int TZ = L == 1024 ? PM_TZ1024 : PM_TZP;
+  static constexpr int NTZ = L == 1024 ? PM_NTZ1024 : L == 512 ? PM_NTZP : L >= 128 ? 128 : 64;
+};
+
+// First- or last-stage elements (radix R) of the block's T columns from / to a
+// uniform base: element j + r L/R of column q is row j + r L/R, ROWB bytes
+// apart.  Uniform base plus a 32-bit offset keeps the addresses out of the
+// vector registers.
+template <int L, int T, int NT, int R, int ROWB>
+__device__ __forceinline__ void load_tile(float2* v, const float2* base, bool on) {
+  using B = Bfly<L, T, NT, R>;
+#pragma unroll
+  for (int u = 0; u < B::BPT; ++u) {
+    const unsigned b = threadIdx.x + u * NT;
+    const bool ok = on && B::valid((int)b);
+    const unsigned o = (b / T) * ROWB + (b % T) * 8;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      v[u * R + r] = ok ? *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(base) + (size_t)r * (L / R) * ROWB + o)
+                        : make_float2(0.0f, 0.0f);
   }
+}
+template <int L, int T, int NT, int R, int ROWB>
+__device__ __forceinline__ void store_tile(const float2* v, float2* base, bool on) {
+  using B = Bfly<L, T, NT, R>;
+  if (!on) return;
+#pragma unroll
+  for (int u = 0; u < B::BPT; ++u) {
+    const unsigned b = threadIdx.x + u * NT;
+    if (!B::valid((int)b)) continue;
+    const unsigned o = (b / T) * ROWB + (b % T) * 8;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      *reinterpret_cast<float2*>(reinterpret_cast<char*>(base) + (size_t)r * (L / R) * ROWB + o) = v[u * R + r];
+  }
+}
+
+// v[u R + r] <- f(v[u R + r], row index) over the elements of a stage (radix R)
+template <int L, int T, int NT, int R, typename F>
+__device__ __forceinline__ void each_row(F&& f) {
+  using B = Bfly<L, T, NT, R>;
+#pragma unroll
+  for (int u = 0; u < B::BPT; ++u) {
+    const int b = threadIdx.x + u * NT;
+    if (!B::valid(b)) continue;
+#pragma unroll
+    for (int r = 0; r < R; ++r) f(u * R + r, b / T + r * (L / R));
+  }
+}
+
+enum { Y_DOT = 0, Y_GRAD = 1, Y_GRAD_ADD = 2 };
+
+// One block: T columns of one z plane.  kd[k]: the wavevector table (kt, or
+// kappa for the Newton field) of both kx and ky.  The components are
+// transformed one after the other, so that two of them (three where the next
+// one's loads are in flight) are in registers at a time.
+template <int L, int T, int NT, int YOP>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES))) void k_ypot(
+    PArgs a, long long comp_stride, int ncols, const float2* __restrict__ tw, Gate gate) {
+  if (gated_off(gate)) return;
+  constexpr int E = ColCfg<L, T, NT>::E, NH = 16 / T, ROWB = 128;
+  extern __shared__ float2 lds[];
+  float2* tw_s = lds + ColBuf<L, T>::elems;
+  float* kd_s = reinterpret_cast<float*>(tw_s + L);
+  // block order as in k_ypass: the forward pass takes planes from the last one
+  // the x pass wrote, the inverse pass groups from the last ones of the z pass
+  const int nt = gridDim.x, nb = gridDim.x * gridDim.y;
+  int b = blockIdx.x + nt * blockIdx.y;
+  // half-line tiles: the two halves of a line on one XCD (see k_zpass)
+  if (NH > 1 && nb % 8 == 0) b = (b % 8) * (nb / 8) + b / 8;
+  int t, z;
+  if constexpr (YOP == Y_DOT) {
+    t = b % nt;
+    z = L - 1 - b / nt;
+  } else if constexpr (NH == 1) {
+    z = b % L;
+    t = nt - 1 - b / L;
+  } else {
+    z = (b / NH) % L;
+    t = (nt / NH - 1 - b / (NH * L)) * NH + b % NH;
+  }
+  const int x0 = t * T;
+  const int nval = min(T, ncols - x0);
+  if (nval <= 0) return;                           // the unused tail of the last group
+  const long long off = ((long long)(x0 >> 4) * L + z) * L * 16 + (x0 & 15);
+  using First = PlanAt<L, false, 0>;
+  using Last = PlanAt<L, false, Plan<L>::S - 1>;
+  constexpr int R0 = First::R, R1 = Last::R;
+  static_assert(NT % T == 0, "a thread's butterflies share a column");
+  const int q = threadIdx.x % T;
+  const bool on = q < nval;
+  float2* f0 = a.f + off;
+  float2* f1 = f0 + comp_stride;
+  float2* f2 = f1 + comp_stride;
+  float2* pa = a.a + off;
+  float2* pb = a.b + off;
+  const float tx = (x0 + q < L / 2) ? a.kd[x0 + q] : 0.0f;
+  constexpr bool INV = YOP != Y_DOT;
+  auto fft = [&](float2* v) { col_fft<L, T, NT, 1, INV, false>(v, lds, tw_s, 1); };
+  float2 v[E], w[E], x[E];
+  load_tile<L, T, NT, R0, ROWB>(v, YOP == Y_DOT ? f0 : pb, on);
+  load_tile<L, T, NT, R0, ROWB>(w, YOP == Y_DOT ? f1 : pa, on);
+  if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1, ROWB>(x, f2, on);
+  load_twiddles<L>(tw_s, tw, NT);
+  for (int i = threadIdx.x; i < L; i += NT) kd_s[i] = a.kd[i];
+  __syncthreads();
+  if constexpr (YOP == Y_DOT) {
+    fft(v);
+    load_tile<L, T, NT, R0, ROWB>(x, f2, on);
+    fft(w);
+    each_row<L, T, NT, R1>([&](int e, int ky) { v[e] = cadd(cscale(v[e], tx), cscale(w[e], kd_s[ky])); });
+    store_tile<L, T, NT, R1, ROWB>(v, pa, on);
+    fft(x);
+    store_tile<L, T, NT, R1, ROWB>(x, pb, on);
+  } else {
+    // z from the pair's second spectrum, then x and y from its first
+    auto put = [&](float2* d, float2* to, float s) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        d[e] = cscale(d[e], s);
+        if constexpr (YOP == Y_GRAD_ADD)
+          d[e] = make_float2(fmaf(x[e].x, a.fscale, d[e].x), fmaf(x[e].y, a.fscale, d[e].y));
+      }
+      store_tile<L, T, NT, R1, ROWB>(d, to, on);
+    };
+    fft(v);
+    put(v, f2, 1.0f);
+    each_row<L, T, NT, R0>([&](int e, int ky) { v[e] = cscale(w[e], kd_s[ky]); });
+    if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1, ROWB>(x, f0, on);
+    fft(w);
+    put(w, f0, tx);
+    if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1, ROWB>(x, f1, on);
+    fft(v);
+    put(v, f1, 1.0f);
+  }
+}
+
+enum { P_NEWTON = 0, P_CURL = 1, P_FINAL = 2, P_DIV = 3 };
+
+// z pass of the potential form; a block owns T columns of one ky row of the
+// pair (a, b), numbered as in k_zpass.
+//   P_NEWTON: rho_hat (in phiN) -> phi_N_hat = -4 pi G A rho_hat (stored in
+//             phiN); pair of -i phi_N / N^3 with kappa_z; Parseval sum of |g_N|^2
+//   P_CURL  : psi = At (A + ktz B) / N^3, pair (psi, ktz psi)
+//   P_FINAL : phi_hat = i psi, one spectrum, into a
+//   P_DIV   : psi = At (kt . g_N - A - ktz B) / N^3, g_N = -i kappa phi_N
+template <int L, int T, int NT, int ZOP>
+__global__ __launch_bounds__(NT) void k_zpot(PArgs a, int ncols, const float2* __restrict__ tw, Gate gate) {
+  if (gated_off(gate)) return;
+  constexpr int E = ColCfg<L, T, NT>::E, NHZ = 16 / T;
+  constexpr int NIN = ZOP == P_NEWTON ? 1 : 2, NOUT = ZOP == P_FINAL ? 1 : 2;
+  extern __shared__ float2 lds[];
+  float2* tw_s = lds + ColBuf<L, T>::elems;
+  const int nb = gridDim.x;
+  const int lb = (nb % 8 == 0) ? (blockIdx.x % 8) * (nb / 8) + blockIdx.x / 8 : blockIdx.x;
+  const int y = (lb / NHZ) % L, x0 = 16 * (lb / (NHZ * L)) + (lb % NHZ) * T;
+  const int nval = min(T, ncols - x0);             // valid columns
+  if (nval <= 0) {                                 // the unused tail of the last group
+    if (ZOP == P_NEWTON && threadIdx.x == 0) a.partials[blockIdx.x] = 0.0;
+    return;
+  }
+  const long long off = ((long long)(x0 >> 4) * L * L + y) * 16 + (x0 & 15);
+  using First = PlanAt<L, false, 0>;
+  using Last = PlanAt<L, false, Plan<L>::S - 1>;
+  static_assert(NT % T == 0, "a thread's butterflies share a column");
+  const int q = threadIdx.x % T, kxi = x0 + q;
+  const bool inb = q < nval;
+  float2 v[2 * E];
+  float2* pa = a.a + off;
+  float2* pb = a.b + off;
+  float2* ph = a.phiN + off;
+  constexpr int R0 = First::R, R1 = Last::R, ROWB = L * 128;
+  float2 php[ZOP == P_DIV ? E : 1];
+  load_tile<L, T, NT, R0, ROWB>(v, ZOP == P_NEWTON ? ph : pa, inb);
+  if constexpr (NIN == 2) load_tile<L, T, NT, R0, ROWB>(v + E, pb, inb);
+  if constexpr (ZOP == P_DIV) load_tile<L, T, NT, R1, ROWB>(php, ph, inb);   // at the operator's elements
+  load_twiddles<L>(tw_s, tw, NT);
+  __syncthreads();
+  col_fft<L, T, NT, NIN, false, false>(v, lds, tw_s, 1);
+
+  double acc = 0.0;
+  const float ky = a.kv[y], ty = a.kt[y], kpy = a.kap[y];
+  const float kx = a.kv[kxi < L ? kxi : 0];
+  const float tx = (kxi < L / 2) ? a.kt[kxi] : 0.0f, kpx = (kxi < L / 2) ? a.kap[kxi] : 0.0f;
+  each_row<L, T, NT, R1>([&](int e, int kz) {
+    if constexpr (ZOP == P_NEWTON) {
+      const float kzz = a.kv[kz], kpz = a.kap[kz];
+      const float k2 = kx * kx + ky * ky + kzz * kzz;
+      const float2 p = cscale(v[e], a.newton_coef * ((k2 > 0.0f) ? hw_rcp(k2) : 0.0f));
+      if (inb) {
+        *reinterpret_cast<float2*>(reinterpret_cast<char*>(ph) + (size_t)kz * ROWB + q * 8) = p;
+        const double w = (kxi == 0 || kxi == L / 2) ? 1.0 : 2.0;
+        const double m2 = (double)p.x * p.x + (double)p.y * p.y;
+        acc += w * m2 * ((double)kpx * kpx + (double)kpy * kpy + (double)kpz * kpz);
+      }
+      v[e] = cscale(mul_mi<false>(p), a.scale);
+      v[E + e] = cscale(v[e], kpz);
+    } else {
+      const float tz = a.kt[kz];
+      const float t2 = tx * tx + ty * ty + tz * tz;
+      const float At = (t2 > 0.0f) ? hw_rcp(t2) * a.scale : 0.0f;
+      float2 d = cadd(v[e], cscale(v[E + e], tz));
+      if constexpr (ZOP == P_DIV) {
+        const float kk = fmaf(tx, kpx, fmaf(ty, kpy, tz * a.kap[kz]));
+        d = csub(cscale(mul_mi<false>(php[e]), kk), d);
+      }
+      v[e] = cscale(ZOP == P_FINAL ? mul_mi<true>(d) : d, At);
+      if constexpr (ZOP != P_FINAL) v[E + e] = cscale(v[e], tz);
+    }
+  });
+  if constexpr (ZOP == P_NEWTON) {
+    __shared__ double red[NT / 64];
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int w = 0; w < NT / 64; ++w) t += red[w];
+      a.partials[blockIdx.x] = t;
+    }
+  }
+  col_fft<L, T, NT, NOUT, true, true>(v, lds, tw_s, 1);
+  store_tile<L, T, NT, R0, ROWB>(v, pa, inb);
+  if constexpr (NOUT == 2) store_tile<L, T, NT, R0, ROWB>(v + E, pb, inb);
 }
 
 // ----------------------------------------------------------------------------
 // host-side launchers
 // ----------------------------------------------------------------------------
-namespace {
+// The passes of one box size are compiled in a translation unit of their own
+// (PM_FFT_PART = n_pad, see build.py); PM_FFT_PART = 0 holds the rest.
+#ifndef PM_FFT_PART
+#define PM_FFT_PART 0
+#endif
 constexpr int kNT = 256;
 constexpr int kNTZ = PM_NTZ;
 
+template <int N>
+hipError_t run_pass(const FftGeom& g, const PassDesc& d, hipStream_t st);
+
+#if PM_FFT_PART
 template <int N>
 struct Cfg {
   static constexpr int H = N / 2;
@@ -1535,9 +1810,38 @@ hipError_t launch_z(const FftGeom& g, ZArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int N, int YOP>
+hipError_t launch_ypot(const FftGeom& g, const PArgs& a, hipStream_t st) {
+  using C = PCfg<N>;
+  const int tiles = (N / 2 + 1 + 15) / 16 * (16 / C::TY);
+  const size_t sh = sizeof(float2) * ((size_t)ColBuf<N, C::TY>::elems + N) + sizeof(float) * N;
+  hipLaunchKernelGGL((k_ypot<N, C::TY, C::NTY, YOP>), dim3(tiles, N), dim3(C::NTY), sh, st, a, g.comp_stride,
+                     N / 2 + 1, g.tw, g.gate);
+  return hipGetLastError();
+}
+
+template <int N>
+constexpr int zp_blocks() { return (N / 2 + 1 + 15) / 16 * (16 / PCfg<N>::TZ) * N; }
+
+template <int N, int ZOP>
+hipError_t launch_zpot(const FftGeom& g, const PArgs& a, hipStream_t st) {
+  using C = PCfg<N>;
+  const size_t sh = sizeof(float2) * ((size_t)ColBuf<N, C::TZ>::elems + N);
+  hipLaunchKernelGGL((k_zpot<N, C::TZ, C::NTZ, ZOP>), dim3(zp_blocks<N>()), dim3(C::NTZ), sh, st, a, N / 2 + 1, g.tw,
+                     g.gate);
+  return hipGetLastError();
+}
+
 template <int N>
 hipError_t run_pass(const FftGeom& g, const PassDesc& d, hipStream_t st) {
   switch (d.kind) {
+    case PASS_Y_DOT: return launch_ypot<N, Y_DOT>(g, d.p, st);
+    case PASS_Y_GRAD: return launch_ypot<N, Y_GRAD>(g, d.p, st);
+    case PASS_Y_GRAD_ADD: return launch_ypot<N, Y_GRAD_ADD>(g, d.p, st);
+    case PASS_P_NEWTON: return launch_zpot<N, P_NEWTON>(g, d.p, st);
+    case PASS_P_CURL: return launch_zpot<N, P_CURL>(g, d.p, st);
+    case PASS_P_FINAL: return launch_zpot<N, P_FINAL>(g, d.p, st);
+    case PASS_P_DIV: return launch_zpot<N, P_DIV>(g, d.p, st);
     case PASS_X_FWD_REAL:
       return launch_x<N, X_FWD_REAL, 1>(g, d.spec, d.real, d.real_cs, 0, 0.f, nullptr, nullptr, st, d.dip);
     case PASS_X_FWD_REAL3:
@@ -1603,7 +1907,26 @@ hipError_t run_pass(const FftGeom& g, const PassDesc& d, hipStream_t st) {
   }
   return hipErrorInvalidValue;
 }
-}  // namespace
+template hipError_t run_pass<PM_FFT_PART>(const FftGeom&, const PassDesc&, hipStream_t);
+#endif
+
+#if !PM_FFT_PART
+// Sum of partials[0..n) into out[0] (FP64), one block.
+__global__ __launch_bounds__(1024) void k_reduce_partials(const double* __restrict__ partials, int n,
+                                                          double* out, Gate gate) {
+  if (gated_off(gate)) return;
+  __shared__ double red[16];
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < n; i += 1024) acc += partials[i];
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < 16; ++w) t += red[w];
+    out[0] = t;
+  }
+}
 
 int x_blocks(int N) {
   if (N == 512) return N * N / XWave<256>::ROWS;
@@ -1617,6 +1940,7 @@ int z_blocks(int N) {
   const int H = N / 2;
   return ((H + 1 + 15) / 16) * (16 / (PM_TZ * PM_HZ)) * N;
 }
+int zpot_blocks(int N) { return ((N / 2 + 1 + 15) / 16) * (16 / (N == 1024 ? PM_TZ1024 : PM_TZP)) * N; }
 int z_blocks_io(int N, int io) {
   const int H = N / 2;
   return io ? ((H + 1 + 15) / 16) * N : z_blocks(N);
@@ -1836,5 +2160,7 @@ hipError_t gate_advance(int* ctl, hipStream_t st) {
   hipLaunchKernelGGL(k_gate_advance, dim3(1), dim3(64), 0, st, ctl);
   return hipGetLastError();
 }
+
+#endif
 
 }  // namespace pm

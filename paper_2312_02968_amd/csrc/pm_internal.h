@@ -37,6 +37,24 @@ struct FftGeom {
   Gate gate{};            // gate of the current launch (set by fft_pass from PassDesc)
 };
 
+// Arguments of the passes in potential form (see pm_fft.hip): two spectra
+// stand for a field of which only the divergence, or only the gradient part,
+// is needed along z.
+struct PArgs {
+  float2* f = nullptr;         // the field's three components, comp_stride apart
+  float2* a = nullptr;         // the pair (in place in the z passes)
+  float2* b = nullptr;
+  float2* phiN = nullptr;
+  const float* kv = nullptr;   // wavevector tables (per axis index)
+  const float* kt = nullptr;
+  const float* kap = nullptr;
+  const float* kd = nullptr;   // y passes: kt, or kap for the Newton field
+  float newton_coef = 0.f;
+  float scale = 0.f;           // 1 / N^3
+  float fscale = 0.f;          // PASS_Y_GRAD_ADD: factor of the field added
+  double* partials = nullptr;
+};
+
 // Arguments of a z pass (see pm_fft.hip).
 struct ZArgs {
   float2* spec;
@@ -60,6 +78,7 @@ enum PassKind {
   PASS_X_FWD_REAL, PASS_X_FWD_REAL3, PASS_X_FWD_COARSE3, PASS_X_INV_REAL, PASS_X_INV_REAL3, PASS_X_NU, PASS_X_MU,
   PASS_X_LIN_NU, PASS_X_LIN_MU, PASS_Z_GRAD,
   PASS_Y_FWD, PASS_Y_INV,
+  PASS_Y_DOT, PASS_Y_GRAD, PASS_Y_GRAD_ADD, PASS_P_NEWTON, PASS_P_CURL, PASS_P_FINAL, PASS_P_DIV,
   PASS_Z_FWD, PASS_Z_INV, PASS_Z_NEWTON, PASS_Z_CURL, PASS_Z_CURL_FINAL, PASS_Z_DIV, PASS_Z_POISSON, PASS_Z_APPARENT, PASS_Z_POISSON_SPEC
 };
 
@@ -94,6 +113,7 @@ struct PassDesc {
   double* partials = nullptr;
   int ncomp = 1;
   ZArgs z{};
+  PArgs p{};                     // the passes in potential form
   // storage of the spectra the pass reads and writes: 0 FP32; 1 FP16 in and
   // out; 2 FP32 in, FP16 out; 3 FP16 in, FP32 out (the half-precision forms
   // exist for the passes of the increment solve)
@@ -126,6 +146,7 @@ hipError_t tol_check(int* ctl, const double* acc, int k, int kmax, double tol, d
 hipError_t gate_advance(int* ctl, hipStream_t st);
 int x_blocks(int N);
 int z_blocks(int N);
+int zpot_blocks(int N);           // z-pass blocks of the potential form
 int z_blocks_io(int N, int io);   // z-pass blocks with half-precision spectra (io != 0)
 
 // ---------------------------------------------------------------------------
