@@ -115,12 +115,14 @@ static int timer_of(PassKind k) {
     case PASS_Y_FWD: return PM_T_Y_FWD;
     case PASS_Y_INV: return PM_T_Y_INV;
     case PASS_Y_DOT: return PM_T_Y_FWD;
+    case PASS_Y_DOT_SUB: return PM_T_Y_FWD;
     case PASS_Y_GRAD: return PM_T_Y_INV;
     case PASS_Y_GRAD_ADD: return PM_T_Y_INV;
     case PASS_P_NEWTON: return PM_T_Z_NEWTON;
     case PASS_P_CURL: return PM_T_Z_CURL;
     case PASS_P_FINAL: return PM_T_Z_CURL_FINAL;
     case PASS_P_DIV: return PM_T_Z_DIV;
+    case PASS_P_SOURCE: return PM_T_Z_NEWTON;
     case PASS_Z_FWD: return PM_T_Z_FWD;
     case PASS_Z_INV: return PM_T_Z_INV;
     case PASS_Z_NEWTON: return PM_T_Z_NEWTON;
@@ -143,6 +145,9 @@ int32_t pm_spectrum_pitch(int32_t n_pad) {
   const int need = n_pad / 2 + 1;
   return (need + 15) & ~15;
 }
+
+// Complex entries of one spectrum of a context (padded planes).
+static size_t spectrum_entries(int N, int P) { return (size_t)(P / 16) * N * (16 * N + plane_pad(N)); }
 
 static pm_status check_params(const pm_params* p) {
   if (!p) return inval("params is NULL");
@@ -239,7 +244,7 @@ static void derive_sizes(pm_ctx* c, const pm_params* p, int64_t max_particles) {
 
 // Assigns every device buffer of the context from cv; returns the bytes used.
 static size_t carve(pm_ctx* c, Carver& cv) {
-  const size_t N = c->N, C = N * N * (size_t)c->P, R = N * N * N;
+  const size_t N = c->N, C = spectrum_entries(c->N, c->P), R = N * N * N;
   const size_t ntiles = (N / 8) * (N / 8) * (N / 8);
   const size_t mp = (size_t)(c->max_particles > 0 ? c->max_particles : 1);
   const size_t nb = (ntiles + 1023) / 1024;
@@ -312,7 +317,7 @@ pm_status pm_create(const pm_params* p, int64_t max_particles, void* workspace, 
   derive_sizes(c, p, max_particles);
   c->st = static_cast<hipStream_t>(stream);
   const int N = c->N;
-  const size_t C = (size_t)N * N * c->P;
+  const size_t C = spectrum_entries(N, c->P);
   const double Rb = p->cutoff * p->sigma;
   std::vector<int> ball = make_ball(Rb), rows = make_rows(Rb);
   const int ext = ball_extent(Rb);
@@ -377,6 +382,7 @@ pm_status pm_create(const pm_params* p, int64_t max_particles, void* workspace, 
 
   c->fg.N = N;
   c->fg.P = c->P;
+  c->fg.ps = 16 * N + plane_pad(N);
   c->fg.comp_stride = (long long)C;
   c->fg.tw = c->tw;
   c->fg.bf16x3 = (p->flags & PM_F_DFT_BF16X3) ? 1 : 0;
@@ -606,6 +612,7 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
     HIPCHK(pass(c, d));
     HIPCHK(reduce_partials(c->partials, z_blocks_io(N, d.io), c->dacc, c->st));
     HIPCHK(pass(c, spec3(PASS_Y_INV)));
+    if (pot && K > 1) HIPCHK(ppass(PASS_P_SOURCE, s0, s1, Gate{}));
   }
   int k_done = 0;
   for (int k = 1; k <= K; ++k) {
@@ -665,7 +672,7 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
       HIPCHK(pass(c, d));
     }
     if (pot) {
-      HIPCHK(ppass(PASS_Y_DOT, w0, w1, run0));
+      HIPCHK(ppass(PASS_Y_DOT_SUB, w0, w1, run0));
       HIPCHK(ppass(PASS_P_DIV, w0, w1, run0));
       HIPCHK(ppass(PASS_Y_GRAD_ADD, w0, w1, run0));
     } else {
@@ -998,11 +1005,17 @@ pm_status pm_diagnostics(pm_ctx* c, const float* pos, const float* vel, const fl
 pm_status pm_fft_r2c(pm_ctx* c, const float* in, void* out) {
   if (!c || !in || !out) return inval("NULL argument");
   float2* sp = static_cast<float2*>(out);
-  PassDesc d = pdesc(PASS_X_FWD_REAL, sp);
+  // the caller's spectrum has unpadded planes
+  auto own = [&](PassKind k) {
+    PassDesc d = pdesc(k, sp, 1);
+    d.ps = 16 * c->N;
+    return d;
+  };
+  PassDesc d = own(PASS_X_FWD_REAL);
   d.real = const_cast<float*>(in);
   HIPCHK(pass(c, d));
-  HIPCHK(pass(c, pdesc(PASS_Y_FWD, sp, 1)));
-  PassDesc z = pdesc(PASS_Z_FWD, sp);
+  HIPCHK(pass(c, own(PASS_Y_FWD)));
+  PassDesc z = own(PASS_Z_FWD);
   z.z = zargs(c);
   z.z.spec = sp;
   z.z.nc = 1;
@@ -1014,12 +1027,17 @@ pm_status pm_fft_c2r(pm_ctx* c, const void* in, float* out) {
   if (!c || !in || !out) return inval("NULL argument");
   const size_t C = (size_t)c->N * c->N * c->P;
   HIPCHK(hipMemcpyAsync(c->spec, in, C * sizeof(float2), hipMemcpyDeviceToDevice, c->st));
-  PassDesc z = pdesc(PASS_Z_INV, c->spec);
+  auto own = [&](PassKind k) {
+    PassDesc d = pdesc(k, c->spec, 1);
+    d.ps = 16 * c->N;
+    return d;
+  };
+  PassDesc z = own(PASS_Z_INV);
   z.z = zargs(c);
   z.z.nc = 1;
   HIPCHK(pass(c, z));
-  HIPCHK(pass(c, pdesc(PASS_Y_INV, c->spec, 1)));
-  PassDesc d = pdesc(PASS_X_INV_REAL, c->spec);
+  HIPCHK(pass(c, own(PASS_Y_INV)));
+  PassDesc d = own(PASS_X_INV_REAL);
   d.real = out;
   HIPCHK(pass(c, d));
   return PM_OK;

@@ -8,7 +8,9 @@
 // kz) then reads one contiguous N * 128-byte run, an x-pass block (16
 // consecutive rows) 2 KB runs, and a z-pass block (half a group, one ky)
 // 64-byte pieces N * 128 bytes apart.  Three-component fields are three such
-// spectra, comp_stride apart.
+// spectra, comp_stride apart.  The context's own spectra pad each plane
+// (plane_pad in pm_internal.h): with planes a power of two apart the z passes'
+// pieces fall on few memory channels.
 //
 // A 3D transform is three passes, one per axis.  The x pass works on whole
 // rows and does the real<->complex step as a half-length complex FFT plus the
@@ -46,9 +48,9 @@ int z_blocks(int N);
 int z_blocks_io(int N, int io);
 
 // Offset of element k of spectrum row `row` (row = kz * N + ky) in the
-// grouped layout; NN = N * N.
-__device__ __forceinline__ long long sidx(long long row, int k, long long NN) {
-  return ((long long)(k >> 4) * NN + row) * 16 + (k & 15);
+// grouped layout; ps: plane stride, N a power of two.
+__device__ __forceinline__ long long sidx(long long row, int k, int N, int ps) {
+  return ((long long)(k >> 4) * N + row / N) * ps + (row & (N - 1)) * 16 + (k & 15);
 }
 
 // ----------------------------------------------------------------------------
@@ -202,7 +204,7 @@ __device__ __forceinline__ void add_dipole(float2& x, const Dipole& dip, long lo
 // IO = 1: the spectrum rows are FP16 (read with the y pass's scales, written
 // with one scale per row and component).
 template <int H, int ROWS, int NC, int NT, int XMODE, int IO = 0>
-__global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_stride,
+__global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_stride, int ps,
                                               float* real, long long real_comp_stride,
                                               const float2* __restrict__ tw, int mu_mode, float inv_a0,
                                               float* fprev, double* partials, Dipole dip,
@@ -214,7 +216,6 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
   extern __shared__ float2 lds[];
   const int row0 = blockIdx.x * ROWS;
   const int N = 2 * H;
-  const long long NN = (long long)N * N;
   float2* tw_s = lds + (H + 1) * IS;
   for (int t = threadIdx.x; t < N; t += NT) tw_s[t] = tw[t];
   const __half2* spec_h = reinterpret_cast<const __half2*>(spec);
@@ -240,18 +241,18 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
       const int q = b / H, k = b % H;
       const int c = q / ROWS, r = q % ROWS;
       if constexpr (IO == 1)
-        lds[k * IS + q] = from_half(spec_h[c * comp_stride + sidx(row0 + r, k, NN)],
+        lds[k * IS + q] = from_half(spec_h[c * comp_stride + sidx(row0 + r, k, N, ps)],
                                     sc.ys[c * sc.ycs + (long long)(k >> 4) * N + (row0 + r) / N]);
       else
-        lds[k * IS + q] = spec[c * comp_stride + sidx(row0 + r, k, NN)];
+        lds[k * IS + q] = spec[c * comp_stride + sidx(row0 + r, k, N, ps)];
     }
     for (int q = threadIdx.x; q < S; q += NT) {
       const int c = q / ROWS, r = q % ROWS;
       if constexpr (IO == 1)
-        lds[H * IS + q] = from_half(spec_h[c * comp_stride + sidx(row0 + r, H, NN)],
+        lds[H * IS + q] = from_half(spec_h[c * comp_stride + sidx(row0 + r, H, N, ps)],
                                     sc.ys[c * sc.ycs + (long long)(H >> 4) * N + (row0 + r) / N]);
       else
-        lds[H * IS + q] = spec[c * comp_stride + sidx(row0 + r, H, NN)];
+        lds[H * IS + q] = spec[c * comp_stride + sidx(row0 + r, H, N, ps)];
     }
   }
   __syncthreads();
@@ -337,21 +338,21 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
       for (int b = threadIdx.x; b < S * H; b += NT) {
         const int q = b / H, k = b % H;
         const int c = q / ROWS, r = q % ROWS;
-        dst_h[c * comp_stride + sidx(row0 + r, k, NN)] = to_half(lds[k * IS + q], inv_s[q]);
+        dst_h[c * comp_stride + sidx(row0 + r, k, N, ps)] = to_half(lds[k * IS + q], inv_s[q]);
       }
       for (int q = threadIdx.x; q < S; q += NT) {
         const int c = q / ROWS, r = q % ROWS;
-        dst_h[c * comp_stride + sidx(row0 + r, H, NN)] = to_half(lds[H * IS + q], inv_s[q]);
+        dst_h[c * comp_stride + sidx(row0 + r, H, N, ps)] = to_half(lds[H * IS + q], inv_s[q]);
       }
     } else {
       for (int b = threadIdx.x; b < S * H; b += NT) {
         const int q = b / H, k = b % H;
         const int c = q / ROWS, r = q % ROWS;
-        spec[c * comp_stride + sidx(row0 + r, k, NN)] = lds[k * IS + q];
+        spec[c * comp_stride + sidx(row0 + r, k, N, ps)] = lds[k * IS + q];
       }
       for (int q = threadIdx.x; q < S; q += NT) {
         const int c = q / ROWS, r = q % ROWS;
-        spec[c * comp_stride + sidx(row0 + r, H, NN)] = lds[H * IS + q];
+        spec[c * comp_stride + sidx(row0 + r, H, N, ps)] = lds[H * IS + q];
       }
     }
   } else {
@@ -552,7 +553,7 @@ struct XWaves {
 };
 
 template <int H, int XMODE, int NC, int IO = 0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, XMODE>::value))) void k_xpass_wave(float2* spec, long long comp_stride, float* real,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, XMODE>::value))) void k_xpass_wave(float2* spec, long long comp_stride, int ps, float* real,
                                                     long long real_comp_stride, const float2* __restrict__ tw,
                                                     int mu_mode, float inv_a0, float* fprev, double* partials,
                                                     Dipole dip, const float* __restrict__ base, Scales sc,
@@ -561,7 +562,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
   using X = XWave<H>;
   using XK = XKind<XMODE>;
   constexpr int N = X::N, LANES = X::LANES, RG = X::RG;
-  constexpr long long NN = (long long)N * N;
   extern __shared__ float2 lds[];
   float2* tw_s = lds;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -603,14 +603,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
           const int k = j + LANES * r;
-          x[r] = from_half(src[sidx(row, k, NN)], ysc[(long long)(k >> 4) * N]);
+          x[r] = from_half(src[sidx(row, k, N, ps)], ysc[(long long)(k >> 4) * N]);
         }
-        nyq = from_half(src[sidx(row, H, NN)], ysc[(long long)(H >> 4) * N]);
+        nyq = from_half(src[sidx(row, H, N, ps)], ysc[(long long)(H >> 4) * N]);
       } else {
         const float2* src = spec + c * comp_stride;
 #pragma unroll
-        for (int r = 0; r < RG; ++r) x[r] = src[sidx(row, j + LANES * r, NN)];
-        nyq = src[sidx(row, H, NN)];
+        for (int r = 0; r < RG; ++r) x[r] = src[sidx(row, j + LANES * r, N, ps)];
+        nyq = src[sidx(row, H, N, ps)];
       }
       // merge: Z[k] = (Xk + conj Xm) + i (Xk - conj Xm) conj(W^k), Xm = X[H - k]
 #pragma unroll
@@ -717,9 +717,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
       const float sc_r = tile_scale(mx), inv = 1.0f / sc_r;
       __half2* dst = reinterpret_cast<__half2*>(spec) + c * comp_stride;
 #pragma unroll
-      for (int r = 0; r < RG; ++r) dst[sidx(row, j + LANES * r, NN)] = to_half(o[r], inv);
+      for (int r = 0; r < RG; ++r) dst[sidx(row, j + LANES * r, N, ps)] = to_half(o[r], inv);
       if (j == 0) {
-        dst[sidx(row, H, NN)] = to_half(nyq, inv);
+        dst[sidx(row, H, N, ps)] = to_half(nyq, inv);
         sc.xs[c * sc.xcs + row] = sc_r;
       }
     } else {
@@ -735,10 +735,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
         const float2 e = cscale(cadd(zk, cconj(zm)), 0.5f);
         const float2 o = cscale(mul_mi<false>(csub(zk, cconj(zm))), 0.5f);
         if (k == 0) {
-          dst[sidx(row, 0, NN)] = make_float2(zk.x + zk.y, 0.0f);
-          dst[sidx(row, H, NN)] = make_float2(zk.x - zk.y, 0.0f);
+          dst[sidx(row, 0, N, ps)] = make_float2(zk.x + zk.y, 0.0f);
+          dst[sidx(row, H, N, ps)] = make_float2(zk.x - zk.y, 0.0f);
         } else {
-          dst[sidx(row, k, NN)] = cadd(e, cmul(tw_s[k], o));
+          dst[sidx(row, k, N, ps)] = cadd(e, cmul(tw_s[k], o));
         }
       }
     }
@@ -888,7 +888,7 @@ __device__ __forceinline__ void cols_absmax(const float2* v, int E, const int* n
 // the LDS exchange buffer (the buffer holds only T columns).  With T = 16 a
 // load instruction covers whole 128-byte rows of consecutive ky.
 template <int L, int T, int NT, bool INV, int IO = 0>
-__global__ __launch_bounds__(NT) void k_ypass(float2* spec, long long comp_stride, int ncols,
+__global__ __launch_bounds__(NT) void k_ypass(float2* spec, long long comp_stride, int ps, int ncols,
                                               const float2* __restrict__ tw, Scales sc, Gate gate) {
   if (gated_off(gate)) return;
   static_assert(16 % T == 0, "a y-pass block owns one group of 16 kx columns");
@@ -916,7 +916,7 @@ __global__ __launch_bounds__(NT) void k_ypass(float2* spec, long long comp_strid
     t = nt - 1 - (int)(b / ((long long)L * nc));
   }
   const int x0 = t * 16;
-  const long long boff = comp * comp_stride + ((long long)t * L + kz) * L * 16;
+  const long long boff = comp * comp_stride + ((long long)t * L + kz) * ps;
   float2* base = spec + boff;
   load_twiddles<L>(tw_s, tw, NT);
   float2 v[NH * E];
@@ -991,7 +991,7 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
 }
 
 template <int L, bool INV>
-__global__ __launch_bounds__(256) void k_ypass_mfma(float2* spec, long long comp_stride, int ncols,
+__global__ __launch_bounds__(256) void k_ypass_mfma(float2* spec, long long comp_stride, int ps, int ncols,
                                                     const float2* __restrict__ tw, Gate gate) {
   if (gated_off(gate)) return;
   constexpr int M = L / 16;
@@ -1017,7 +1017,7 @@ __global__ __launch_bounds__(256) void k_ypass_mfma(float2* spec, long long comp
     t = nt - 1 - (int)(b / ((long long)L * nc));
   }
   const int nv = min(16, ncols - t * 16);
-  float2* base = spec + comp * comp_stride + ((long long)t * L + kz) * L * 16;
+  float2* base = spec + comp * comp_stride + ((long long)t * L + kz) * ps;
   load_twiddles<L>(tw_s, tw, 256);
   for (int i = threadIdx.x; i < L * 16; i += 256) {
     const int r = i >> 4, c = i & 15;
@@ -1172,8 +1172,8 @@ __global__ __launch_bounds__(NT) void k_zpass(ZArgs a, const float2* __restrict_
     if (a.partials && threadIdx.x == 0) a.partials[blockIdx.x] = 0.0;
     return;
   }
-  const long long row = (long long)L * 16;                                  // kz stride
-  const long long off = ((long long)(x0 >> 4) * L * L + y) * 16 + (x0 & 15);
+  const long long row = a.ps;                                               // kz stride
+  const long long off = (long long)(x0 >> 4) * L * row + y * 16 + (x0 & 15);
   load_twiddles<L>(tw_s, tw, NT);
   int nvh[HZ];
   const int nvalid = min(16, a.ncols - x0);           // valid columns of an interleaved group
@@ -1453,9 +1453,11 @@ __global__ __launch_bounds__(NT) void k_zpass(ZArgs a, const float2* __restrict_
 // Newton field -i kappa phi_N has the same form with kappa in place of kt.
 // For the divergence-free step the x pass's output F'(kx, y, z) stays where it
 // is and Y_GRAD_ADD adds the correction to it, so F' takes no part in the y and
-// z transforms' rounding.  Bytes per half iteration in spectra of one
-// component: curl-free 5 + 4 + 5 (18 in components), divergence-free
-// 5 + 5 + 8 (19), and four z transforms per column instead of six.
+// z transforms' rounding.  Its kt . g_N is the same in every iteration: the
+// Newton pass leaves it transformed back to z (S), Y_DOT_SUB subtracts from it,
+// and both projections share one z pass.  Bytes per half iteration in spectra
+// of one component: curl-free 5 + 4 + 5 (18 in components), divergence-free
+// 6 + 4 + 8 (19), and four z transforms per column instead of six.
 // ----------------------------------------------------------------------------
 #ifndef PM_NTYP
 #define PM_NTYP 1024
@@ -1473,10 +1475,10 @@ __global__ __launch_bounds__(NT) void k_zpass(ZArgs a, const float2* __restrict_
 #define PM_NTY1024 1024
 #endif
 #ifndef PM_NTZ1024
-#define PM_NTZ1024 1024
+#define PM_NTZ1024 512
 #endif
 #ifndef PM_TZ1024
-#define PM_TZ1024 16
+#define PM_TZ1024 8
 #endif
 #ifndef PM_TZP
 #define PM_TZP 8
@@ -1488,9 +1490,9 @@ __global__ __launch_bounds__(NT) void k_zpass(ZArgs a, const float2* __restrict_
 // 1024^3 (ms per K = 4 solve).  y: 16 columns (whole 128-byte lines) with 1024
 // threads at 512 (20.4; 512 threads 20.4, 8 columns 20.9); at 1024 the registers
 // of 16 columns spill (212) and 8 are taken (195; with 512 threads 198).  z: 8
-// columns with 512 threads at 512 (16 columns 20.6 to 20.8 against 20.3); at
-// 1024 16 columns with 1024 threads (193 against 195).  Below, as many threads
-// as a radix stage has butterflies, so that no wave of a block idles (the
+// columns with 512 threads (at 512, 16 columns 20.6 to 20.8 against 20.3; at
+// 1024 two such blocks share a CU, z pass 4.3 ms against 4.7 with 16 columns
+// and 1024 threads).  Below, as many threads as a radix stage has butterflies, so that no wave of a block idles (the
 // plans of 64 to 256 points have 8 to 16 butterflies per column).
 template <int L>
 struct PCfg {
@@ -1501,35 +1503,35 @@ struct PCfg {
 };
 
 // First- or last-stage elements (radix R) of the block's T columns from / to a
-// uniform base: element j + r L/R of column q is row j + r L/R, ROWB bytes
+// uniform base: element j + r L/R of column q is row j + r L/R, rowb bytes
 // apart.  Uniform base plus a 32-bit offset keeps the addresses out of the
 // vector registers.
-template <int L, int T, int NT, int R, int ROWB>
-__device__ __forceinline__ void load_tile(float2* v, const float2* base, bool on) {
+template <int L, int T, int NT, int R>
+__device__ __forceinline__ void load_tile(float2* v, const float2* base, unsigned rowb, bool on) {
   using B = Bfly<L, T, NT, R>;
 #pragma unroll
   for (int u = 0; u < B::BPT; ++u) {
     const unsigned b = threadIdx.x + u * NT;
     const bool ok = on && B::valid((int)b);
-    const unsigned o = (b / T) * ROWB + (b % T) * 8;
+    const unsigned o = (b / T) * rowb + (b % T) * 8;
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      v[u * R + r] = ok ? *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(base) + (size_t)r * (L / R) * ROWB + o)
+      v[u * R + r] = ok ? *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(base) + (size_t)r * (L / R) * rowb + o)
                         : make_float2(0.0f, 0.0f);
   }
 }
-template <int L, int T, int NT, int R, int ROWB>
-__device__ __forceinline__ void store_tile(const float2* v, float2* base, bool on) {
+template <int L, int T, int NT, int R>
+__device__ __forceinline__ void store_tile(const float2* v, float2* base, unsigned rowb, bool on) {
   using B = Bfly<L, T, NT, R>;
   if (!on) return;
 #pragma unroll
   for (int u = 0; u < B::BPT; ++u) {
     const unsigned b = threadIdx.x + u * NT;
     if (!B::valid((int)b)) continue;
-    const unsigned o = (b / T) * ROWB + (b % T) * 8;
+    const unsigned o = (b / T) * rowb + (b % T) * 8;
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      *reinterpret_cast<float2*>(reinterpret_cast<char*>(base) + (size_t)r * (L / R) * ROWB + o) = v[u * R + r];
+      *reinterpret_cast<float2*>(reinterpret_cast<char*>(base) + (size_t)r * (L / R) * rowb + o) = v[u * R + r];
   }
 }
 
@@ -1546,7 +1548,7 @@ __device__ __forceinline__ void each_row(F&& f) {
   }
 }
 
-enum { Y_DOT = 0, Y_GRAD = 1, Y_GRAD_ADD = 2 };
+enum { Y_DOT = 0, Y_GRAD = 1, Y_GRAD_ADD = 2, Y_DOT_SUB = 3 };
 
 // One block: T columns of one z plane.  kd[k]: the wavevector table (kt, or
 // kappa for the Newton field) of both kx and ky.  The components are
@@ -1554,9 +1556,11 @@ enum { Y_DOT = 0, Y_GRAD = 1, Y_GRAD_ADD = 2 };
 // one's loads are in flight) are in registers at a time.
 template <int L, int T, int NT, int YOP>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES))) void k_ypot(
-    PArgs a, long long comp_stride, int ncols, const float2* __restrict__ tw, Gate gate) {
+    PArgs a, long long comp_stride, int ps, int ncols, const float2* __restrict__ tw, Gate gate) {
   if (gated_off(gate)) return;
-  constexpr int E = ColCfg<L, T, NT>::E, NH = 16 / T, ROWB = 128;
+  constexpr int E = ColCfg<L, T, NT>::E, NH = 16 / T;
+  constexpr bool DOT = YOP == Y_DOT || YOP == Y_DOT_SUB;
+  constexpr unsigned rowb = 128;
   extern __shared__ float2 lds[];
   float2* tw_s = lds + ColBuf<L, T>::elems;
   float* kd_s = reinterpret_cast<float*>(tw_s + L);
@@ -1567,7 +1571,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES)
   // half-line tiles: the two halves of a line on one XCD (see k_zpass)
   if (NH > 1 && nb % 8 == 0) b = (b % 8) * (nb / 8) + b / 8;
   int t, z;
-  if constexpr (YOP == Y_DOT) {
+  if constexpr (DOT) {
     t = b % nt;
     z = L - 1 - b / nt;
   } else if constexpr (NH == 1) {
@@ -1580,7 +1584,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES)
   const int x0 = t * T;
   const int nval = min(T, ncols - x0);
   if (nval <= 0) return;                           // the unused tail of the last group
-  const long long off = ((long long)(x0 >> 4) * L + z) * L * 16 + (x0 & 15);
+  const long long off = ((long long)(x0 >> 4) * L + z) * ps + (x0 & 15);
   using First = PlanAt<L, false, 0>;
   using Last = PlanAt<L, false, Plan<L>::S - 1>;
   constexpr int R0 = First::R, R1 = Last::R;
@@ -1593,23 +1597,32 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES)
   float2* pa = a.a + off;
   float2* pb = a.b + off;
   const float tx = (x0 + q < L / 2) ? a.kd[x0 + q] : 0.0f;
-  constexpr bool INV = YOP != Y_DOT;
+  constexpr bool INV = !DOT;
   auto fft = [&](float2* v) { col_fft<L, T, NT, 1, INV, false>(v, lds, tw_s, 1); };
   float2 v[E], w[E], x[E];
-  load_tile<L, T, NT, R0, ROWB>(v, YOP == Y_DOT ? f0 : pb, on);
-  load_tile<L, T, NT, R0, ROWB>(w, YOP == Y_DOT ? f1 : pa, on);
-  if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1, ROWB>(x, f2, on);
+  load_tile<L, T, NT, R0>(v, DOT ? f0 : pb, rowb, on);
+  load_tile<L, T, NT, R0>(w, DOT ? f1 : pa, rowb, on);
+  if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1>(x, f2, rowb, on);
   load_twiddles<L>(tw_s, tw, NT);
   for (int i = threadIdx.x; i < L; i += NT) kd_s[i] = a.kd[i];
   __syncthreads();
-  if constexpr (YOP == Y_DOT) {
+  if constexpr (DOT) {
     fft(v);
-    load_tile<L, T, NT, R0, ROWB>(x, f2, on);
+    load_tile<L, T, NT, R0>(x, f2, rowb, on);
     fft(w);
-    each_row<L, T, NT, R1>([&](int e, int ky) { v[e] = cadd(cscale(v[e], tx), cscale(w[e], kd_s[ky])); });
-    store_tile<L, T, NT, R1, ROWB>(v, pa, on);
+    float2 src[YOP == Y_DOT_SUB ? E : 1];
+    if constexpr (YOP == Y_DOT_SUB) load_tile<L, T, NT, R1>(src, a.phiN + off, rowb, on);
+    each_row<L, T, NT, R1>([&](int e, int ky) {
+      v[e] = cadd(cscale(v[e], tx), cscale(w[e], kd_s[ky]));
+      if constexpr (YOP == Y_DOT_SUB) v[e] = csub(src[e], v[e]);
+    });
+    store_tile<L, T, NT, R1>(v, pa, rowb, on);
     fft(x);
-    store_tile<L, T, NT, R1, ROWB>(x, pb, on);
+    if constexpr (YOP == Y_DOT_SUB) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] = cscale(x[e], -1.0f);
+    }
+    store_tile<L, T, NT, R1>(x, pb, rowb, on);
   } else {
     // z from the pair's second spectrum, then x and y from its first
     auto put = [&](float2* d, float2* to, float s) {
@@ -1619,34 +1632,38 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES)
         if constexpr (YOP == Y_GRAD_ADD)
           d[e] = make_float2(fmaf(x[e].x, a.fscale, d[e].x), fmaf(x[e].y, a.fscale, d[e].y));
       }
-      store_tile<L, T, NT, R1, ROWB>(d, to, on);
+      store_tile<L, T, NT, R1>(d, to, rowb, on);
     };
     fft(v);
     put(v, f2, 1.0f);
     each_row<L, T, NT, R0>([&](int e, int ky) { v[e] = cscale(w[e], kd_s[ky]); });
-    if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1, ROWB>(x, f0, on);
+    if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1>(x, f0, rowb, on);
     fft(w);
     put(w, f0, tx);
-    if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1, ROWB>(x, f1, on);
+    if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1>(x, f1, rowb, on);
     fft(v);
     put(v, f1, 1.0f);
   }
 }
 
-enum { P_NEWTON = 0, P_CURL = 1, P_FINAL = 2, P_DIV = 3 };
+enum { P_NEWTON = 0, P_PAIR = 1, P_FINAL = 2, P_SOURCE = 3 };
 
 // z pass of the potential form; a block owns T columns of one ky row of the
 // pair (a, b), numbered as in k_zpass.
-//   P_NEWTON: rho_hat (in phiN) -> phi_N_hat = -4 pi G A rho_hat (stored in
-//             phiN); pair of -i phi_N / N^3 with kappa_z; Parseval sum of |g_N|^2
-//   P_CURL  : psi = At (A + ktz B) / N^3, pair (psi, ktz psi)
+//   P_NEWTON: rho_hat (in phiN) -> phi_N_hat = -4 pi G A rho_hat; pair of
+//             -i phi_N / N^3 with kappa_z; S = invz (kt . g_N) / N into phiN;
+//             Parseval sum of |g_N|^2
+//   P_PAIR  : psi = At (A + ktz B) / N^3, pair (psi, ktz psi)
 //   P_FINAL : phi_hat = i psi, one spectrum, into a
-//   P_DIV   : psi = At (kt . g_N - A - ktz B) / N^3, g_N = -i kappa phi_N
+//   P_SOURCE: S from phi_N_hat, both in phiN (after a start in component form)
+// At L = 1024 two blocks share a CU when a block keeps to 128 registers and
+// 80 KB of LDS, so the Parseval sum goes through the exchange buffer.
 template <int L, int T, int NT, int ZOP>
-__global__ __launch_bounds__(NT) void k_zpot(PArgs a, int ncols, const float2* __restrict__ tw, Gate gate) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 4 : 1))) void k_zpot(
+    PArgs a, int ps, int ncols, const float2* __restrict__ tw, Gate gate) {
   if (gated_off(gate)) return;
   constexpr int E = ColCfg<L, T, NT>::E, NHZ = 16 / T;
-  constexpr int NIN = ZOP == P_NEWTON ? 1 : 2, NOUT = ZOP == P_FINAL ? 1 : 2;
+  constexpr bool PAIR = ZOP == P_PAIR || ZOP == P_FINAL;      // two spectra in
   extern __shared__ float2 lds[];
   float2* tw_s = lds + ColBuf<L, T>::elems;
   const int nb = gridDim.x;
@@ -1657,57 +1674,58 @@ __global__ __launch_bounds__(NT) void k_zpot(PArgs a, int ncols, const float2* _
     if (ZOP == P_NEWTON && threadIdx.x == 0) a.partials[blockIdx.x] = 0.0;
     return;
   }
-  const long long off = ((long long)(x0 >> 4) * L * L + y) * 16 + (x0 & 15);
+  const long long off = (long long)(x0 >> 4) * L * ps + y * 16 + (x0 & 15);
   using First = PlanAt<L, false, 0>;
   using Last = PlanAt<L, false, Plan<L>::S - 1>;
+  constexpr int R0 = First::R, R1 = Last::R;
   static_assert(NT % T == 0, "a thread's butterflies share a column");
   const int q = threadIdx.x % T, kxi = x0 + q;
   const bool inb = q < nval;
-  float2 v[2 * E];
+  const unsigned rowb = ps * 8u;                   // bytes from one kz to the next
   float2* pa = a.a + off;
   float2* pb = a.b + off;
   float2* ph = a.phiN + off;
-  constexpr int R0 = First::R, R1 = Last::R, ROWB = L * 128;
-  float2 php[ZOP == P_DIV ? E : 1];
-  load_tile<L, T, NT, R0, ROWB>(v, ZOP == P_NEWTON ? ph : pa, inb);
-  if constexpr (NIN == 2) load_tile<L, T, NT, R0, ROWB>(v + E, pb, inb);
-  if constexpr (ZOP == P_DIV) load_tile<L, T, NT, R1, ROWB>(php, ph, inb);   // at the operator's elements
+  float2 v[(ZOP == P_SOURCE ? 1 : 2) * E];
+  // (P_SOURCE has no forward transform: its elements are the operator's)
+  load_tile<L, T, NT, ZOP == P_SOURCE ? R1 : R0>(v, PAIR ? pa : ph, rowb, inb);
+  if constexpr (PAIR) load_tile<L, T, NT, R0>(v + E, pb, rowb, inb);
   load_twiddles<L>(tw_s, tw, NT);
   __syncthreads();
-  col_fft<L, T, NT, NIN, false, false>(v, lds, tw_s, 1);
+  if constexpr (ZOP != P_SOURCE) col_fft<L, T, NT, PAIR ? 2 : 1, false, false>(v, lds, tw_s, 1);
 
   double acc = 0.0;
   const float ky = a.kv[y], ty = a.kt[y], kpy = a.kap[y];
   const float kx = a.kv[kxi < L ? kxi : 0];
   const float tx = (kxi < L / 2) ? a.kt[kxi] : 0.0f, kpx = (kxi < L / 2) ? a.kap[kxi] : 0.0f;
+  // -i phi_N (kt . kappa) / N, the spectrum of S, from phi_N_hat
+  auto source = [&](float2 p, float tz, float kpz) {
+    return cscale(mul_mi<false>(p), fmaf(tx, kpx, fmaf(ty, kpy, tz * kpz)) * (1.0f / L));
+  };
   each_row<L, T, NT, R1>([&](int e, int kz) {
     if constexpr (ZOP == P_NEWTON) {
       const float kzz = a.kv[kz], kpz = a.kap[kz];
       const float k2 = kx * kx + ky * ky + kzz * kzz;
       const float2 p = cscale(v[e], a.newton_coef * ((k2 > 0.0f) ? hw_rcp(k2) : 0.0f));
       if (inb) {
-        *reinterpret_cast<float2*>(reinterpret_cast<char*>(ph) + (size_t)kz * ROWB + q * 8) = p;
         const double w = (kxi == 0 || kxi == L / 2) ? 1.0 : 2.0;
         const double m2 = (double)p.x * p.x + (double)p.y * p.y;
         acc += w * m2 * ((double)kpx * kpx + (double)kpy * kpy + (double)kpz * kpz);
       }
       v[e] = cscale(mul_mi<false>(p), a.scale);
-      v[E + e] = cscale(v[e], kpz);
+      v[E + e] = source(p, a.kt[kz], kpz);
+    } else if constexpr (ZOP == P_SOURCE) {
+      v[e] = source(v[e], a.kt[kz], a.kap[kz]);
     } else {
       const float tz = a.kt[kz];
       const float t2 = tx * tx + ty * ty + tz * tz;
       const float At = (t2 > 0.0f) ? hw_rcp(t2) * a.scale : 0.0f;
-      float2 d = cadd(v[e], cscale(v[E + e], tz));
-      if constexpr (ZOP == P_DIV) {
-        const float kk = fmaf(tx, kpx, fmaf(ty, kpy, tz * a.kap[kz]));
-        d = csub(cscale(mul_mi<false>(php[e]), kk), d);
-      }
+      const float2 d = cadd(v[e], cscale(v[E + e], tz));
       v[e] = cscale(ZOP == P_FINAL ? mul_mi<true>(d) : d, At);
-      if constexpr (ZOP != P_FINAL) v[E + e] = cscale(v[e], tz);
+      if constexpr (ZOP == P_PAIR) v[E + e] = cscale(v[e], tz);
     }
   });
   if constexpr (ZOP == P_NEWTON) {
-    __shared__ double red[NT / 64];
+    double* red = reinterpret_cast<double*>(lds);  // the exchange buffer is free between the transforms
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
@@ -1716,10 +1734,15 @@ __global__ __launch_bounds__(NT) void k_zpot(PArgs a, int ncols, const float2* _
       for (int w = 0; w < NT / 64; ++w) t += red[w];
       a.partials[blockIdx.x] = t;
     }
+    __syncthreads();
+    col_fft<L, T, NT, 1, true, true>(v + E, lds, tw_s, 1);
+    store_tile<L, T, NT, R0>(v + E, ph, rowb, inb);
+    each_row<L, T, NT, R1>([&](int e, int kz) { v[E + e] = cscale(v[e], a.kap[kz]); });
   }
+  constexpr int NOUT = ZOP == P_NEWTON || ZOP == P_PAIR ? 2 : 1;
   col_fft<L, T, NT, NOUT, true, true>(v, lds, tw_s, 1);
-  store_tile<L, T, NT, R0, ROWB>(v, pa, inb);
-  if constexpr (NOUT == 2) store_tile<L, T, NT, R0, ROWB>(v + E, pb, inb);
+  store_tile<L, T, NT, R0>(v, ZOP == P_SOURCE ? ph : pa, rowb, inb);
+  if constexpr (NOUT == 2) store_tile<L, T, NT, R0>(v + E, pb, rowb, inb);
 }
 
 // ----------------------------------------------------------------------------
@@ -1754,14 +1777,14 @@ hipError_t launch_x(const FftGeom& g, float2* spec, float* real, long long real_
     using X = XWave<N / 2>;
     const size_t sh = sizeof(float2) * (N + (size_t)X::ROWS * X::XB + X::TWL);
     hipLaunchKernelGGL((k_xpass_wave<N / 2, XMODE, NC, IO>), dim3(N * N / X::ROWS), dim3(256), sh, st, spec,
-                       g.comp_stride, real, real_cs, g.tw, mu_mode, inv_a0, fprev, partials, dip, base, g.sc,
+                       g.comp_stride, g.ps, real, real_cs, g.tw, mu_mode, inv_a0, fprev, partials, dip, base, g.sc,
                        g.gate, co);
     return hipGetLastError();
   } else {
     const int blocks = N * N / C::ROWS;
     const size_t sh = sizeof(float2) * ((size_t)(C::H + 1) * (NC * C::ROWS + 1) + N);
     hipLaunchKernelGGL((k_xpass<C::H, C::ROWS, NC, kNT, XMODE, IO>), dim3(blocks), dim3(kNT), sh, st, spec,
-                       g.comp_stride, real, real_cs, g.tw, mu_mode, inv_a0, fprev, partials, dip, base, g.sc,
+                       g.comp_stride, g.ps, real, real_cs, g.tw, mu_mode, inv_a0, fprev, partials, dip, base, g.sc,
                        g.gate, co);
     return hipGetLastError();
   }
@@ -1774,7 +1797,7 @@ hipError_t launch_y(const FftGeom& g, float2* spec, int ncomp, hipStream_t st) {
   const int tiles = (C::H + 1 + 15) / 16;
   const size_t sh = sizeof(float2) * ((size_t)ColBuf<N, TY>::elems + N);
   hipLaunchKernelGGL((k_ypass<N, TY, kNT, INV, IO>), dim3(tiles, N, ncomp), dim3(kNT), sh, st, spec,
-                     g.comp_stride, C::H + 1, g.tw, g.sc, g.gate);
+                     g.comp_stride, g.ps, C::H + 1, g.tw, g.sc, g.gate);
   return hipGetLastError();
 }
 
@@ -1785,7 +1808,7 @@ hipError_t launch_y_mfma(const FftGeom& g, float2* spec, int ncomp, hipStream_t 
     constexpr size_t xe = (size_t)N * 17 > (size_t)M * 260 ? (size_t)N * 17 : (size_t)M * 260;
     const int tiles = (N / 2 + 1 + 15) / 16;
     hipLaunchKernelGGL((k_ypass_mfma<N, INV>), dim3(tiles, N, ncomp), dim3(256), sizeof(float2) * (xe + N), st,
-                       spec, g.comp_stride, N / 2 + 1, g.tw, g.gate);
+                       spec, g.comp_stride, g.ps, N / 2 + 1, g.tw, g.gate);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -1796,6 +1819,7 @@ template <int N, int ZOP, int IO = 0>
 hipError_t launch_z(const FftGeom& g, ZArgs a, hipStream_t st) {
   using C = Cfg<N>;
   a.comp_stride = g.comp_stride;
+  a.ps = g.ps;
   a.ncols = C::H + 1;
   if constexpr (IO != 0) {
     // half-precision spectra: a block owns a whole group of 16 kx
@@ -1815,7 +1839,7 @@ hipError_t launch_ypot(const FftGeom& g, const PArgs& a, hipStream_t st) {
   using C = PCfg<N>;
   const int tiles = (N / 2 + 1 + 15) / 16 * (16 / C::TY);
   const size_t sh = sizeof(float2) * ((size_t)ColBuf<N, C::TY>::elems + N) + sizeof(float) * N;
-  hipLaunchKernelGGL((k_ypot<N, C::TY, C::NTY, YOP>), dim3(tiles, N), dim3(C::NTY), sh, st, a, g.comp_stride,
+  hipLaunchKernelGGL((k_ypot<N, C::TY, C::NTY, YOP>), dim3(tiles, N), dim3(C::NTY), sh, st, a, g.comp_stride, g.ps,
                      N / 2 + 1, g.tw, g.gate);
   return hipGetLastError();
 }
@@ -1827,7 +1851,7 @@ template <int N, int ZOP>
 hipError_t launch_zpot(const FftGeom& g, const PArgs& a, hipStream_t st) {
   using C = PCfg<N>;
   const size_t sh = sizeof(float2) * ((size_t)ColBuf<N, C::TZ>::elems + N);
-  hipLaunchKernelGGL((k_zpot<N, C::TZ, C::NTZ, ZOP>), dim3(zp_blocks<N>()), dim3(C::NTZ), sh, st, a, N / 2 + 1, g.tw,
+  hipLaunchKernelGGL((k_zpot<N, C::TZ, C::NTZ, ZOP>), dim3(zp_blocks<N>()), dim3(C::NTZ), sh, st, a, g.ps, N / 2 + 1, g.tw,
                      g.gate);
   return hipGetLastError();
 }
@@ -1836,12 +1860,14 @@ template <int N>
 hipError_t run_pass(const FftGeom& g, const PassDesc& d, hipStream_t st) {
   switch (d.kind) {
     case PASS_Y_DOT: return launch_ypot<N, Y_DOT>(g, d.p, st);
+    case PASS_Y_DOT_SUB: return launch_ypot<N, Y_DOT_SUB>(g, d.p, st);
     case PASS_Y_GRAD: return launch_ypot<N, Y_GRAD>(g, d.p, st);
     case PASS_Y_GRAD_ADD: return launch_ypot<N, Y_GRAD_ADD>(g, d.p, st);
     case PASS_P_NEWTON: return launch_zpot<N, P_NEWTON>(g, d.p, st);
-    case PASS_P_CURL: return launch_zpot<N, P_CURL>(g, d.p, st);
+    case PASS_P_CURL: return launch_zpot<N, P_PAIR>(g, d.p, st);
     case PASS_P_FINAL: return launch_zpot<N, P_FINAL>(g, d.p, st);
-    case PASS_P_DIV: return launch_zpot<N, P_DIV>(g, d.p, st);
+    case PASS_P_DIV: return launch_zpot<N, P_PAIR>(g, d.p, st);
+    case PASS_P_SOURCE: return launch_zpot<N, P_SOURCE>(g, d.p, st);
     case PASS_X_FWD_REAL:
       return launch_x<N, X_FWD_REAL, 1>(g, d.spec, d.real, d.real_cs, 0, 0.f, nullptr, nullptr, st, d.dip);
     case PASS_X_FWD_REAL3:
@@ -1949,6 +1975,7 @@ int z_blocks_io(int N, int io) {
 hipError_t fft_pass(const FftGeom& g0, const PassDesc& d, hipStream_t st) {
   FftGeom g = g0;
   g.gate = d.gate;
+  if (d.ps) g.ps = d.ps;
   switch (g.N) {
     case 16: return run_pass<16>(g, d, st);
     case 32: return run_pass<32>(g, d, st);
@@ -2017,7 +2044,7 @@ __global__ __launch_bounds__(256) void k_coarse_spec(const float* __restrict__ y
 // conjugate at -K, which no other thread writes.
 template <int FB>
 __global__ __launch_bounds__(256) void k_feat_spec(const float2* __restrict__ ph, const float* __restrict__ kap,
-                                                    const float2* __restrict__ tw, int N, int n, float2* cs) {
+                                                    const float2* __restrict__ tw, int N, int ps, int n, float2* cs) {
   const int hx = n / 2 + 1;
   const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
   if (t >= (long long)hx * n * n) return;
@@ -2037,10 +2064,10 @@ __global__ __launch_bounds__(256) void k_feat_spec(const float2* __restrict__ ph
         const int kx = Kx + n * mx;
         float2 v;
         if (kx <= N / 2) {
-          v = ph[((long long)((kx >> 4) * N + kz) * N + ky) * 16 + (kx & 15)];
+          v = ph[(long long)((kx >> 4) * N + kz) * ps + ky * 16 + (kx & 15)];
         } else {
           const int cx = N - kx, cy = (N - ky) & (N - 1), cz = (N - kz) & (N - 1);
-          v = cconj(ph[((long long)((cx >> 4) * N + cz) * N + cy) * 16 + (cx & 15)]);
+          v = cconj(ph[(long long)((cx >> 4) * N + cz) * ps + cy * 16 + (cx & 15)]);
         }
         const float2 w = cmul(v, cconj(cmul(block_sum(tw, kx, FB, N), byz)));   // phi_hat conj(B)
         const float2 mw = mul_mi<false>(w);                                      // -i phi_hat conj(B)
@@ -2096,8 +2123,8 @@ hipError_t coarse_features(const FftGeom& g, const float2* phihat, const float* 
   const int fb = g.N / n;
   const long long modes = (long long)(n / 2 + 1) * n * n;
   const dim3 grid((unsigned)((modes + 255) / 256));
-  if (fb == 2) hipLaunchKernelGGL((k_feat_spec<2>), grid, dim3(256), 0, st, phihat, kap, g.tw, g.N, n, cs);
-  else if (fb == 4) hipLaunchKernelGGL((k_feat_spec<4>), grid, dim3(256), 0, st, phihat, kap, g.tw, g.N, n, cs);
+  if (fb == 2) hipLaunchKernelGGL((k_feat_spec<2>), grid, dim3(256), 0, st, phihat, kap, g.tw, g.N, g.ps, n, cs);
+  else if (fb == 4) hipLaunchKernelGGL((k_feat_spec<4>), grid, dim3(256), 0, st, phihat, kap, g.tw, g.N, g.ps, n, cs);
   else return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

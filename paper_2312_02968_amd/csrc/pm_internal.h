@@ -26,11 +26,21 @@ struct Gate {
   int mask = 0;
 };
 
+// Complex entries added to each plane of 16 N of the context's spectra.  A z
+// pass reads one or half a line of every plane; in the 1024^3 box, with planes
+// 128 KB apart, these fall on few of the memory channels (a copy with the
+// pattern of two spectra in place: 3.9 TB/s, 5.0 with 2 KB between planes).  At
+// 512^3 and below the z passes gain 1 to 4 % from padding and the x and y
+// passes lose as much (solve 20.3 ms unpadded, 20.7 to 21.0 padded).
+constexpr int plane_pad(int N) { return N == 1024 ? 256 : 0; }
+
 // Geometry of the FFT box and its half spectrum.
 struct FftGeom {
   int N;                  // n_pad
   int P;                  // kx slots of a spectrum: 16 * ceil((N/2 + 1) / 16)
-  long long comp_stride;  // complex entries per spectrum component (N * N * P)
+  int ps;                 // complex entries from one plane of a group to the next: 16 N + plane_pad(N),
+                          // or 16 N in the layout pm_fft_r2c and pm_fft_c2r exchange
+  long long comp_stride;  // complex entries per spectrum component (N * P / 16 * ps)
   const float2* tw;       // exp(-2 pi i t / N), t < N
   int bf16x3 = 0;         // y passes with the radix-16 stage on the matrix cores (BF16x3)
   Scales sc{};            // scale tables of the half-precision spectra
@@ -44,7 +54,7 @@ struct PArgs {
   float2* f = nullptr;         // the field's three components, comp_stride apart
   float2* a = nullptr;         // the pair (in place in the z passes)
   float2* b = nullptr;
-  float2* phiN = nullptr;
+  float2* phiN = nullptr;      // rho_hat, then S (pm_fft.hip)
   const float* kv = nullptr;   // wavevector tables (per axis index)
   const float* kt = nullptr;
   const float* kap = nullptr;
@@ -60,6 +70,7 @@ struct ZArgs {
   float2* spec;
   float2* out = nullptr;   // FP32 output spectrum when it differs from spec (half-precision input)
   long long comp_stride;
+  int ps;
   int ncols;
   float2* phiN;
   const float* kv;
@@ -78,7 +89,8 @@ enum PassKind {
   PASS_X_FWD_REAL, PASS_X_FWD_REAL3, PASS_X_FWD_COARSE3, PASS_X_INV_REAL, PASS_X_INV_REAL3, PASS_X_NU, PASS_X_MU,
   PASS_X_LIN_NU, PASS_X_LIN_MU, PASS_Z_GRAD,
   PASS_Y_FWD, PASS_Y_INV,
-  PASS_Y_DOT, PASS_Y_GRAD, PASS_Y_GRAD_ADD, PASS_P_NEWTON, PASS_P_CURL, PASS_P_FINAL, PASS_P_DIV,
+  PASS_Y_DOT, PASS_Y_DOT_SUB, PASS_Y_GRAD, PASS_Y_GRAD_ADD, PASS_P_NEWTON, PASS_P_CURL, PASS_P_FINAL, PASS_P_DIV,
+  PASS_P_SOURCE,
   PASS_Z_FWD, PASS_Z_INV, PASS_Z_NEWTON, PASS_Z_CURL, PASS_Z_CURL_FINAL, PASS_Z_DIV, PASS_Z_POISSON, PASS_Z_APPARENT, PASS_Z_POISSON_SPEC
 };
 
@@ -121,6 +133,7 @@ struct PassDesc {
   const float* base = nullptr;   // PASS_X_LIN_*: the field linearised about, [3][N^3]
   Coarse co{};                   // PASS_X_FWD_COARSE3
   Gate gate{};
+  int ps = 0;                    // plane stride of spec if not the context's
 };
 
 hipError_t fft_pass(const FftGeom& g, const PassDesc& d, hipStream_t st);
