@@ -41,7 +41,8 @@ struct pm_ctx {
   float* rho = nullptr;       // internal real grids of pm_step
   float* phi = nullptr;
   float* fprev = nullptr;     // previous F for the residual and the warm start (optional)
-  bool have_F = false;        // fprev holds the last F of a solve
+  float2* fspec = nullptr;    // previous F for the warm start without residuals, as (kx, y, z) spectra
+  bool have_F = false;        // fprev (or fspec) holds the last F of a solve
   float* scales = nullptr;    // scale tables of the increment solve's half-precision spectra
   int* ctl = nullptr;         // tolerance-mode control words (see tol_check)
   double* partials = nullptr;
@@ -123,6 +124,7 @@ static int timer_of(PassKind k) {
     case PASS_P_FINAL: return PM_T_Z_CURL_FINAL;
     case PASS_P_DIV: return PM_T_Z_DIV;
     case PASS_P_SOURCE: return PM_T_Z_NEWTON;
+    case PASS_P_WARM: return PM_T_Z_NEWTON;
     case PASS_Z_FWD: return PM_T_Z_FWD;
     case PASS_Z_INV: return PM_T_Z_INV;
     case PASS_Z_NEWTON: return PM_T_Z_NEWTON;
@@ -254,7 +256,10 @@ static size_t carve(pm_ctx* c, Carver& cv) {
   // (a one-component spectrum is a little larger than a grid)
   c->rho = cv.take<float>(R > 2 * C ? R : 2 * C);
   c->phi = cv.take<float>(R > 2 * C ? R : 2 * C);
-  c->fprev = (need_residual(c->p) || (c->p.flags & PM_F_WARM_START)) ? cv.take<float>(3 * R) : nullptr;
+  const bool warm = (c->p.flags & PM_F_WARM_START) != 0;
+  const bool spec_warm = warm && !need_residual(c->p) && !(c->p.flags & PM_F_DFT_BF16X3);
+  c->fprev = (need_residual(c->p) || (warm && !spec_warm)) ? cv.take<float>(3 * R) : nullptr;
+  c->fspec = spec_warm ? cv.take<float2>(3 * C) : nullptr;
   c->scales = cv.take<float>(scale_floats((int)N, c->P));
   c->ctl = cv.take<int>(16);
   c->partials = cv.take<double>((size_t)c->npartials);
@@ -471,6 +476,7 @@ static PassDesc ppdesc(pm_ctx* c, PassKind k, float2* a, float2* b, const float*
   d.gate = gate;
   const double N = c->N;
   d.p.f = c->spec;
+  d.p.fout = c->spec;
   d.p.a = a;
   d.p.b = b;
   d.p.phiN = c->phiN;
@@ -564,7 +570,11 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
   // warm start: F0 = P_L g_N + P_T F_prev from the last F of the previous solve
   const bool keep_F = !inc && (p.flags & PM_F_WARM_START) != 0;
   const bool warm = keep_F && c->have_F && !H0 && !learned;
-  const float* start = inc ? nullptr : (H0 ? H0 : (warm ? c->fprev : nullptr));
+  // (without residuals F is kept as its spectrum along x, which the warm
+  // start takes up in the y pass: F as a real field would go through an x pass
+  // each way)
+  const bool spec_warm = warm && c->fspec;
+  const float* start = inc ? nullptr : (H0 ? H0 : (warm && !spec_warm ? c->fprev : nullptr));
   if (start) {
     PassDesc d = pdesc(PASS_X_FWD_REAL3, c->spec);
     d.real = const_cast<float*>(start);
@@ -595,7 +605,16 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
   float2* w0 = reinterpret_cast<float2*>(c->rho);
   float2* w1 = reinterpret_cast<float2*>(c->phi);
   auto ppass = [&](PassKind k, float2* a, float2* b, Gate gate) { return pass(c, ppdesc(c, k, a, b, c->kt, gate)); };
-  if (pot && !start && !learned) {
+  if (spec_warm) {
+    PassDesc d = ppdesc(c, PASS_Y_DOT, w0, w1, c->kt, Gate{});
+    d.p.f = c->fspec;
+    HIPCHK(pass(c, d));
+    HIPCHK(ppass(PASS_P_WARM, w0, w1, Gate{}));
+    HIPCHK(reduce_partials(c->partials, zpot_blocks(N), c->dacc, c->st));
+    d.kind = PASS_Y_GRAD_ADD;
+    d.p.fscale = 1.0f;
+    HIPCHK(pass(c, d));
+  } else if (pot && !start && !learned) {
     HIPCHK(pass(c, ppdesc(c, PASS_P_NEWTON, s0, s1, c->kap, Gate{})));
     HIPCHK(reduce_partials(c->partials, zpot_blocks(N), c->dacc, c->st));
     HIPCHK(pass(c, ppdesc(c, PASS_Y_GRAD, s0, s1, c->kap, run0)));
@@ -623,10 +642,12 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
       d.base = inc ? inc->F : nullptr;
       // F (or dF) is kept every iteration for the residual; for the warm start
       // (or the caller's dF) only the last one
+      // (the residual has a predecessor from the second iteration on)
       if (resid) d.fprev = c->fprev;
-      else if (keep_F && k == K) d.fprev = c->fprev;
+      else if (keep_F && !c->fspec && k == K) d.fprev = c->fprev;
       else if (inc && inc->dF && k == K) d.fprev = inc->dF;
-      d.partials = c->partials;
+      d.partials = resid && k >= 2 ? c->partials : nullptr;
+      if (keep_F && c->fspec && k == K) d.spec_in = c->fspec;
       HIPCHK(pass(c, d));
     }
     if (resid && k >= 2) HIPCHK(reduce_partials(c->partials, x_blocks(N), c->dacc + (k - 1), c->st, run0));
@@ -674,7 +695,9 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
     if (pot) {
       HIPCHK(ppass(PASS_Y_DOT_SUB, w0, w1, run0));
       HIPCHK(ppass(PASS_P_DIV, w0, w1, run0));
-      HIPCHK(ppass(PASS_Y_GRAD_ADD, w0, w1, run0));
+      PassDesc d = ppdesc(c, PASS_Y_GRAD_ADD, w0, w1, c->kt, run0);
+      if (keep_F && c->fspec && k == K - 1) d.p.fout = c->fspec;      // the last F stays there
+      HIPCHK(pass(c, d));
     } else {
       HIPCHK(pass(c, spec3(PASS_Y_FWD)));
       PassDesc d = spec3(PASS_Z_DIV);
@@ -1121,11 +1144,18 @@ pm_status aqual_solve_field(pm_ctx* c, const float* rho, const float* H0, float*
                             pm_solve_info* info) {
   if (!c) return inval("ctx is NULL");
   if (!rho || !phi || !F) return inval("rho, phi and F are required");
-  if (!c->fprev) return inval("aqual_solve_field needs a context created with PM_F_RESIDUAL or tol > 0");
+  if (!c->fprev && !c->fspec) return inval("aqual_solve_field needs a context created with PM_F_RESIDUAL or tol > 0");
   pm_status s = run_solve(c, rho, H0, phi, info, info != nullptr);
   if (s != PM_OK) return s;
   if (info) info->bounds_flag = 0;
   const size_t R = (size_t)c->N * c->N * c->N;
+  if (!c->fprev) {                                 // a warm-start context keeps F as its spectrum along x
+    PassDesc d = pdesc(PASS_X_INV_REAL3, c->fspec);
+    d.real = F;
+    d.real_cs = (long long)R;
+    HIPCHK(pass(c, d));
+    return PM_OK;
+  }
   HIPCHK(hipMemcpyAsync(F, c->fprev, 3 * R * sizeof(float), hipMemcpyDeviceToDevice, c->st));
   return PM_OK;
 }

@@ -199,12 +199,13 @@ __device__ __forceinline__ void add_dipole(float2& x, const Dipole& dip, long lo
 //   X_FUSED_*  : spectrum rows -> c2r -> nu or mu on the 3-vector -> r2c ->
 //                spectrum rows (in place).  X_FUSED_NU_KEEP is X_FUSED_NU that
 //                also accumulates the squared change of F against fprev in
-//                FP64 into partials[blockIdx.x] and stores F to fprev.
+//                FP64 into partials[blockIdx.x] (if not null) and stores F to
+//                fprev.
 //   X_LIN_*    : as X_FUSED_* with the linearised maps about `base`.
 // IO = 1: the spectrum rows are FP16 (read with the y pass's scales, written
 // with one scale per row and component).
 template <int H, int ROWS, int NC, int NT, int XMODE, int IO = 0>
-__global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_stride, int ps,
+__global__ __launch_bounds__(NT) void k_xpass(float2* spec, const float2* spec_in, long long comp_stride, int ps,
                                               float* real, long long real_comp_stride,
                                               const float2* __restrict__ tw, int mu_mode, float inv_a0,
                                               float* fprev, double* partials, Dipole dip,
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
   const int N = 2 * H;
   float2* tw_s = lds + (H + 1) * IS;
   for (int t = threadIdx.x; t < N; t += NT) tw_s[t] = tw[t];
-  const __half2* spec_h = reinterpret_cast<const __half2*>(spec);
+  const __half2* spec_h = reinterpret_cast<const __half2*>(spec_in);
 
   // ---- load
   if (XMODE == X_FWD_COARSE) {
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
         lds[k * IS + q] = from_half(spec_h[c * comp_stride + sidx(row0 + r, k, N, ps)],
                                     sc.ys[c * sc.ycs + (long long)(k >> 4) * N + (row0 + r) / N]);
       else
-        lds[k * IS + q] = spec[c * comp_stride + sidx(row0 + r, k, N, ps)];
+        lds[k * IS + q] = spec_in[c * comp_stride + sidx(row0 + r, k, N, ps)];
     }
     for (int q = threadIdx.x; q < S; q += NT) {
       const int c = q / ROWS, r = q % ROWS;
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
         lds[H * IS + q] = from_half(spec_h[c * comp_stride + sidx(row0 + r, H, N, ps)],
                                     sc.ys[c * sc.ycs + (long long)(H >> 4) * N + (row0 + r) / N]);
       else
-        lds[H * IS + q] = spec[c * comp_stride + sidx(row0 + r, H, N, ps)];
+        lds[H * IS + q] = spec_in[c * comp_stride + sidx(row0 + r, H, N, ps)];
     }
   }
   __syncthreads();
@@ -274,10 +275,12 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
         float2* f0 = reinterpret_cast<float2*>(fprev + e);
         float2* f1 = reinterpret_cast<float2*>(fprev + cs + e);
         float2* f2 = reinterpret_cast<float2*>(fprev + 2 * cs + e);
-        const float2 p0 = *f0, p1 = *f1, p2 = *f2;
-        const double d0 = (double)v0.x - p0.x, d1 = (double)v1.x - p1.x, d2 = (double)v2.x - p2.x;
-        const double e0 = (double)v0.y - p0.y, e1 = (double)v1.y - p1.y, e2 = (double)v2.y - p2.y;
-        acc += d0 * d0 + d1 * d1 + d2 * d2 + e0 * e0 + e1 * e1 + e2 * e2;
+        if (partials) {
+          const float2 p0 = *f0, p1 = *f1, p2 = *f2;
+          const double d0 = (double)v0.x - p0.x, d1 = (double)v1.x - p1.x, d2 = (double)v2.x - p2.x;
+          const double e0 = (double)v0.y - p0.y, e1 = (double)v1.y - p1.y, e2 = (double)v2.y - p2.y;
+          acc += d0 * d0 + d1 * d1 + d2 * d2 + e0 * e0 + e1 * e1 + e2 * e2;
+        }
         *f0 = v0; *f1 = v1; *f2 = v2;
       }
       // two grid points per complex entry: .x is x = 2m, .y is x = 2m+1
@@ -303,7 +306,7 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, long long comp_strid
       lds[m * IS + ROWS + r] = v1;
       lds[m * IS + 2 * ROWS + r] = v2;
     }
-    if (XK::keep) {
+    if (XK::keep && partials) {
       // block reduction of acc (FP64)
       __shared__ double red[NT / 64];
       for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
@@ -553,7 +556,7 @@ struct XWaves {
 };
 
 template <int H, int XMODE, int NC, int IO = 0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, XMODE>::value))) void k_xpass_wave(float2* spec, long long comp_stride, int ps, float* real,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, XMODE>::value))) void k_xpass_wave(float2* spec, const float2* spec_in, long long comp_stride, int ps, float* real,
                                                     long long real_comp_stride, const float2* __restrict__ tw,
                                                     int mu_mode, float inv_a0, float* fprev, double* partials,
                                                     Dipole dip, const float* __restrict__ base, Scales sc,
@@ -598,7 +601,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
       float2 x[RG];
       float2 nyq;
       if constexpr (IO == 1) {
-        const __half2* src = reinterpret_cast<const __half2*>(spec) + c * comp_stride;
+        const __half2* src = reinterpret_cast<const __half2*>(spec_in) + c * comp_stride;
         const float* ysc = sc.ys + c * sc.ycs + row / N;
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
@@ -607,7 +610,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
         }
         nyq = from_half(src[sidx(row, H, N, ps)], ysc[(long long)(H >> 4) * N]);
       } else {
-        const float2* src = spec + c * comp_stride;
+        const float2* src = spec_in + c * comp_stride;
 #pragma unroll
         for (int r = 0; r < RG; ++r) x[r] = src[sidx(row, j + LANES * r, N, ps)];
         nyq = src[sidx(row, H, N, ps)];
@@ -641,10 +644,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
         float2* f0 = reinterpret_cast<float2*>(fprev + e);
         float2* f1 = reinterpret_cast<float2*>(fprev + cs + e);
         float2* f2 = reinterpret_cast<float2*>(fprev + 2 * cs + e);
-        const float2 p0 = *f0, p1 = *f1, p2 = *f2;
-        const double d0 = (double)e0.x - p0.x, d1 = (double)e1.x - p1.x, d2 = (double)e2.x - p2.x;
-        const double g0 = (double)e0.y - p0.y, g1 = (double)e1.y - p1.y, g2 = (double)e2.y - p2.y;
-        acc += d0 * d0 + d1 * d1 + d2 * d2 + g0 * g0 + g1 * g1 + g2 * g2;
+        if (partials) {
+          const float2 p0 = *f0, p1 = *f1, p2 = *f2;
+          const double d0 = (double)e0.x - p0.x, d1 = (double)e1.x - p1.x, d2 = (double)e2.x - p2.x;
+          const double g0 = (double)e0.y - p0.y, g1 = (double)e1.y - p1.y, g2 = (double)e2.y - p2.y;
+          acc += d0 * d0 + d1 * d1 + d2 * d2 + g0 * g0 + g1 * g1 + g2 * g2;
+        }
         *f0 = e0; *f1 = e1; *f2 = e2;
       }
       if constexpr (XK::lin) {
@@ -666,7 +671,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
         v[2][r] = make_float2(e2.x * f0, e2.y * f1);
       }
     }
-    if (XK::keep) {
+    if (XK::keep && partials) {
       __shared__ double red[4];
       for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
       if (lane == 0) red[wave] = acc;
@@ -1591,9 +1596,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES)
   static_assert(NT % T == 0, "a thread's butterflies share a column");
   const int q = threadIdx.x % T;
   const bool on = q < nval;
-  float2* f0 = a.f + off;
-  float2* f1 = f0 + comp_stride;
-  float2* f2 = f1 + comp_stride;
+  const float2* f0 = a.f + off;
+  const float2* f1 = f0 + comp_stride;
+  const float2* f2 = f1 + comp_stride;
+  float2* o0 = a.fout + off;
+  float2* o1 = o0 + comp_stride;
+  float2* o2 = o1 + comp_stride;
   float2* pa = a.a + off;
   float2* pb = a.b + off;
   const float tx = (x0 + q < L / 2) ? a.kd[x0 + q] : 0.0f;
@@ -1635,18 +1643,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PM_YP_WAVES)
       store_tile<L, T, NT, R1>(d, to, rowb, on);
     };
     fft(v);
-    put(v, f2, 1.0f);
+    put(v, o2, 1.0f);
     each_row<L, T, NT, R0>([&](int e, int ky) { v[e] = cscale(w[e], kd_s[ky]); });
     if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1>(x, f0, rowb, on);
     fft(w);
-    put(w, f0, tx);
+    put(w, o0, tx);
     if constexpr (YOP == Y_GRAD_ADD) load_tile<L, T, NT, R1>(x, f1, rowb, on);
     fft(v);
-    put(v, f1, 1.0f);
+    put(v, o1, 1.0f);
   }
 }
 
-enum { P_NEWTON = 0, P_PAIR = 1, P_FINAL = 2, P_SOURCE = 3 };
+enum { P_NEWTON = 0, P_PAIR = 1, P_FINAL = 2, P_SOURCE = 3, P_WARM = 4 };
 
 // z pass of the potential form; a block owns T columns of one ky row of the
 // pair (a, b), numbered as in k_zpass.
@@ -1656,10 +1664,14 @@ enum { P_NEWTON = 0, P_PAIR = 1, P_FINAL = 2, P_SOURCE = 3 };
 //   P_PAIR  : psi = At (A + ktz B) / N^3, pair (psi, ktz psi)
 //   P_FINAL : phi_hat = i psi, one spectrum, into a
 //   P_SOURCE: S from phi_N_hat, both in phiN (after a start in component form)
+//   P_WARM  : as P_NEWTON with the pair (A, B) of the previous solve's F given
+//             (F as the spectrum whose inverse x transform it is, 1/N of its
+//             transform): F0 = P_L g_N + P_T F_prev = F_prev + kt psi with
+//             psi = At kt . (g_N - F_prev)
 // At L = 1024 two blocks share a CU when a block keeps to 128 registers and
 // 80 KB of LDS, so the Parseval sum goes through the exchange buffer.
 template <int L, int T, int NT, int ZOP>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 4 : 1))) void k_zpot(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 && ZOP != P_WARM ? 4 : 1))) void k_zpot(
     PArgs a, int ps, int ncols, const float2* __restrict__ tw, Gate gate) {
   if (gated_off(gate)) return;
   constexpr int E = ColCfg<L, T, NT>::E, NHZ = 16 / T;
@@ -1671,7 +1683,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 
   const int y = (lb / NHZ) % L, x0 = 16 * (lb / (NHZ * L)) + (lb % NHZ) * T;
   const int nval = min(T, ncols - x0);             // valid columns
   if (nval <= 0) {                                 // the unused tail of the last group
-    if (ZOP == P_NEWTON && threadIdx.x == 0) a.partials[blockIdx.x] = 0.0;
+    if ((ZOP == P_NEWTON || ZOP == P_WARM) && threadIdx.x == 0) a.partials[blockIdx.x] = 0.0;
     return;
   }
   const long long off = (long long)(x0 >> 4) * L * ps + y * 16 + (x0 & 15);
@@ -1685,13 +1697,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 
   float2* pa = a.a + off;
   float2* pb = a.b + off;
   float2* ph = a.phiN + off;
-  float2 v[(ZOP == P_SOURCE ? 1 : 2) * E];
+  constexpr bool RHO = ZOP == P_NEWTON || ZOP == P_WARM;      // starts from rho_hat
+  float2 v[(ZOP == P_SOURCE ? 1 : ZOP == P_WARM ? 3 : 2) * E];
   // (P_SOURCE has no forward transform: its elements are the operator's)
   load_tile<L, T, NT, ZOP == P_SOURCE ? R1 : R0>(v, PAIR ? pa : ph, rowb, inb);
   if constexpr (PAIR) load_tile<L, T, NT, R0>(v + E, pb, rowb, inb);
+  if constexpr (ZOP == P_WARM) {
+    load_tile<L, T, NT, R0>(v + E, pa, rowb, inb);
+    load_tile<L, T, NT, R0>(v + 2 * E, pb, rowb, inb);
+  }
   load_twiddles<L>(tw_s, tw, NT);
   __syncthreads();
-  if constexpr (ZOP != P_SOURCE) col_fft<L, T, NT, PAIR ? 2 : 1, false, false>(v, lds, tw_s, 1);
+  if constexpr (ZOP != P_SOURCE) col_fft<L, T, NT, PAIR ? 2 : ZOP == P_WARM ? 3 : 1, false, false>(v, lds, tw_s, 1);
 
   double acc = 0.0;
   const float ky = a.kv[y], ty = a.kt[y], kpy = a.kap[y];
@@ -1702,7 +1719,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 
     return cscale(mul_mi<false>(p), fmaf(tx, kpx, fmaf(ty, kpy, tz * kpz)) * (1.0f / L));
   };
   each_row<L, T, NT, R1>([&](int e, int kz) {
-    if constexpr (ZOP == P_NEWTON) {
+    if constexpr (RHO) {
       const float kzz = a.kv[kz], kpz = a.kap[kz];
       const float k2 = kx * kx + ky * ky + kzz * kzz;
       const float2 p = cscale(v[e], a.newton_coef * ((k2 > 0.0f) ? hw_rcp(k2) : 0.0f));
@@ -1711,8 +1728,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 
         const double m2 = (double)p.x * p.x + (double)p.y * p.y;
         acc += w * m2 * ((double)kpx * kpx + (double)kpy * kpy + (double)kpz * kpz);
       }
-      v[e] = cscale(mul_mi<false>(p), a.scale);
-      v[E + e] = source(p, a.kt[kz], kpz);
+      if constexpr (ZOP == P_NEWTON) {
+        v[e] = cscale(mul_mi<false>(p), a.scale);
+        v[E + e] = source(p, a.kt[kz], kpz);
+      } else {
+        const float tz = a.kt[kz];
+        const float t2 = tx * tx + ty * ty + tz * tz;
+        const float At = (t2 > 0.0f) ? hw_rcp(t2) * (a.scale * L) : 0.0f;
+        const float2 s = source(p, tz, kpz);
+        v[E + e] = cscale(csub(s, cadd(v[E + e], cscale(v[2 * E + e], tz))), At);
+        v[2 * E + e] = cscale(v[E + e], tz);
+        v[e] = s;
+      }
     } else if constexpr (ZOP == P_SOURCE) {
       v[e] = source(v[e], a.kt[kz], a.kap[kz]);
     } else {
@@ -1724,7 +1751,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 
       if constexpr (ZOP == P_PAIR) v[E + e] = cscale(v[e], tz);
     }
   });
-  if constexpr (ZOP == P_NEWTON) {
+  if constexpr (RHO) {
     double* red = reinterpret_cast<double*>(lds);  // the exchange buffer is free between the transforms
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -1735,14 +1762,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(L == 1024 ? 
       a.partials[blockIdx.x] = t;
     }
     __syncthreads();
-    col_fft<L, T, NT, 1, true, true>(v + E, lds, tw_s, 1);
-    store_tile<L, T, NT, R0>(v + E, ph, rowb, inb);
-    each_row<L, T, NT, R1>([&](int e, int kz) { v[E + e] = cscale(v[e], a.kap[kz]); });
+    constexpr int s = ZOP == P_NEWTON ? E : 0;     // the slot of S
+    col_fft<L, T, NT, 1, true, true>(v + s, lds, tw_s, 1);
+    store_tile<L, T, NT, R0>(v + s, ph, rowb, inb);
+    if constexpr (ZOP == P_NEWTON)
+      each_row<L, T, NT, R1>([&](int e, int kz) { v[E + e] = cscale(v[e], a.kap[kz]); });
   }
-  constexpr int NOUT = ZOP == P_NEWTON || ZOP == P_PAIR ? 2 : 1;
-  col_fft<L, T, NT, NOUT, true, true>(v, lds, tw_s, 1);
-  store_tile<L, T, NT, R0>(v, ZOP == P_SOURCE ? ph : pa, rowb, inb);
-  if constexpr (NOUT == 2) store_tile<L, T, NT, R0>(v + E, pb, rowb, inb);
+  constexpr int NOUT = RHO || ZOP == P_PAIR ? 2 : 1;
+  float2* o = v + (ZOP == P_WARM ? E : 0);
+  col_fft<L, T, NT, NOUT, true, true>(o, lds, tw_s, 1);
+  store_tile<L, T, NT, R0>(o, ZOP == P_SOURCE ? ph : pa, rowb, inb);
+  if constexpr (NOUT == 2) store_tile<L, T, NT, R0>(o + E, pb, rowb, inb);
 }
 
 // ----------------------------------------------------------------------------
@@ -1771,19 +1801,20 @@ struct Cfg {
 template <int N, int XMODE, int NC, int IO = 0>
 hipError_t launch_x(const FftGeom& g, float2* spec, float* real, long long real_cs, int mu_mode,
                     float inv_a0, float* fprev, double* partials, hipStream_t st, Dipole dip = Dipole{},
-                    const float* base = nullptr, Coarse co = Coarse{}) {
+                    const float* base = nullptr, Coarse co = Coarse{}, const float2* spec_in = nullptr) {
+  if (!spec_in) spec_in = spec;
   using C = Cfg<N>;
   if constexpr (N == 512 || N == 1024) {
     using X = XWave<N / 2>;
     const size_t sh = sizeof(float2) * (N + (size_t)X::ROWS * X::XB + X::TWL);
-    hipLaunchKernelGGL((k_xpass_wave<N / 2, XMODE, NC, IO>), dim3(N * N / X::ROWS), dim3(256), sh, st, spec,
+    hipLaunchKernelGGL((k_xpass_wave<N / 2, XMODE, NC, IO>), dim3(N * N / X::ROWS), dim3(256), sh, st, spec, spec_in,
                        g.comp_stride, g.ps, real, real_cs, g.tw, mu_mode, inv_a0, fprev, partials, dip, base, g.sc,
                        g.gate, co);
     return hipGetLastError();
   } else {
     const int blocks = N * N / C::ROWS;
     const size_t sh = sizeof(float2) * ((size_t)(C::H + 1) * (NC * C::ROWS + 1) + N);
-    hipLaunchKernelGGL((k_xpass<C::H, C::ROWS, NC, kNT, XMODE, IO>), dim3(blocks), dim3(kNT), sh, st, spec,
+    hipLaunchKernelGGL((k_xpass<C::H, C::ROWS, NC, kNT, XMODE, IO>), dim3(blocks), dim3(kNT), sh, st, spec, spec_in,
                        g.comp_stride, g.ps, real, real_cs, g.tw, mu_mode, inv_a0, fprev, partials, dip, base, g.sc,
                        g.gate, co);
     return hipGetLastError();
@@ -1867,6 +1898,7 @@ hipError_t run_pass(const FftGeom& g, const PassDesc& d, hipStream_t st) {
     case PASS_P_CURL: return launch_zpot<N, P_PAIR>(g, d.p, st);
     case PASS_P_FINAL: return launch_zpot<N, P_FINAL>(g, d.p, st);
     case PASS_P_DIV: return launch_zpot<N, P_PAIR>(g, d.p, st);
+    case PASS_P_WARM: return launch_zpot<N, P_WARM>(g, d.p, st);
     case PASS_P_SOURCE: return launch_zpot<N, P_SOURCE>(g, d.p, st);
     case PASS_X_FWD_REAL:
       return launch_x<N, X_FWD_REAL, 1>(g, d.spec, d.real, d.real_cs, 0, 0.f, nullptr, nullptr, st, d.dip);
@@ -1883,7 +1915,8 @@ hipError_t run_pass(const FftGeom& g, const PassDesc& d, hipStream_t st) {
     case PASS_X_NU:
       if (d.fprev)
         return launch_x<N, X_FUSED_NU_KEEP, 3>(g, d.spec, nullptr, 0, d.mu_mode, d.inv_a0, d.fprev, d.partials, st);
-      return launch_x<N, X_FUSED_NU, 3>(g, d.spec, nullptr, 0, d.mu_mode, d.inv_a0, nullptr, nullptr, st);
+      return launch_x<N, X_FUSED_NU, 3>(g, d.spec, nullptr, 0, d.mu_mode, d.inv_a0, nullptr, nullptr, st, Dipole{},
+                                        nullptr, Coarse{}, d.spec_in);
     case PASS_X_MU:
       return launch_x<N, X_FUSED_MU, 3>(g, d.spec, nullptr, 0, d.mu_mode, d.inv_a0, nullptr, nullptr, st);
     case PASS_X_LIN_NU:

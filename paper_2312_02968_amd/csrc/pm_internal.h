@@ -51,7 +51,8 @@ struct FftGeom {
 // stand for a field of which only the divergence, or only the gradient part,
 // is needed along z.
 struct PArgs {
-  float2* f = nullptr;         // the field's three components, comp_stride apart
+  const float2* f = nullptr;   // the field's three components, comp_stride apart
+  float2* fout = nullptr;      // and where the inverse y passes write it
   float2* a = nullptr;         // the pair (in place in the z passes)
   float2* b = nullptr;
   float2* phiN = nullptr;      // rho_hat, then S (pm_fft.hip)
@@ -90,7 +91,7 @@ enum PassKind {
   PASS_X_LIN_NU, PASS_X_LIN_MU, PASS_Z_GRAD,
   PASS_Y_FWD, PASS_Y_INV,
   PASS_Y_DOT, PASS_Y_DOT_SUB, PASS_Y_GRAD, PASS_Y_GRAD_ADD, PASS_P_NEWTON, PASS_P_CURL, PASS_P_FINAL, PASS_P_DIV,
-  PASS_P_SOURCE,
+  PASS_P_SOURCE, PASS_P_WARM,
   PASS_Z_FWD, PASS_Z_INV, PASS_Z_NEWTON, PASS_Z_CURL, PASS_Z_CURL_FINAL, PASS_Z_DIV, PASS_Z_POISSON, PASS_Z_APPARENT, PASS_Z_POISSON_SPEC
 };
 
@@ -133,6 +134,7 @@ struct PassDesc {
   const float* base = nullptr;   // PASS_X_LIN_*: the field linearised about, [3][N^3]
   Coarse co{};                   // PASS_X_FWD_COARSE3
   Gate gate{};
+  const float2* spec_in = nullptr;   // PASS_X_NU (FP32): read from here instead of spec
   int ps = 0;                    // plane stride of spec if not the context's
 };
 
