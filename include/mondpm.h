@@ -140,13 +140,14 @@ pm_status pm_destroy(pm_ctx* ctx);
  * overwritten.  Each particle adds m_i w_id / s^3 to the cells c_i + d of its
  * ball (central pixel c_i = floor(x_i/s + 1/2) per axis), with w the Gaussian
  * weights normalised by their FP64 sum over the ball (or the literal prefactor
- * with PM_F_ANALYTIC_NORM).  For the balls of radius 4 sigma with sigma = 1
- * or 1.5 cells, every cell is an exact fixed-point sum per 8^3 tile of
+ * with PM_F_ANALYTIC_NORM).  For the balls that reach 1 to 8 cells (radius
+ * above 1 and up to 9), every cell is an exact fixed-point sum per 8^3 tile of
  * particles, rounded to FP32 once per tile and added in a fixed order, so
  * rho is the same bits for any order of the particles (as long as the tiles'
  * pieces of at most 1024 particles fit the context's 2 GB of staging; pieces
  * beyond it, and other balls, add their cells with FP32 atomics, whose last
- * bits vary from run to run).  N <= max_particles. */
+ * bits vary from run to run).  A particle whose mass or position is not finite
+ * makes its ball's cells so.  N <= max_particles. */
 pm_status pm_deposit(pm_ctx* ctx, const float* pos, const float* mass, int64_t N, float* rho);
 
 /* MOND potential phi from rho by the fixed-point iteration of Sect. 2.1:

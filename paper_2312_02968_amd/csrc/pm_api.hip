@@ -61,11 +61,9 @@ struct pm_ctx {
   KernelGeom kg{};
   SortBufs sb{};
   PieceBufs pb{};
-  int piece_ext = 0;          // compiled ball shape of the tile-piece deposit, 0: none
-  int plan_ext = 0;           // the ball's extent if the tile-piece gather takes it, 0: none
+  int plan_ext = 0;           // the ball's extent if the tile-piece kernels take it, 0: none
   int* rowtab = nullptr;      // rows of the ball
   int nrows = 0;
-  int64_t perm_n = -1;        // sb.perm is a permutation of [0, perm_n) from the last sort
   int npartials = 0;
   hipGraphExec_t step_graph = nullptr;  // one captured pm_step (pm_step_capture)
   Dipole dip{};               // external-field sheets added to every Newton solve's density
@@ -224,21 +222,16 @@ static void derive_sizes(pm_ctx* c, const pm_params* p, int64_t max_particles) {
   c->nball = (int)make_ball(p->cutoff * p->sigma).size();
   c->nrows = (int)make_rows(p->cutoff * p->sigma).size();
   c->npartials = x_blocks(c->N) > z_blocks(c->N) ? x_blocks(c->N) : z_blocks(c->N);
-  // The tile-piece kernels are compiled for the balls |d|^2 < 16 and < 36
-  // (radius 4 sigma at sigma = 1 and 1.5 cells): any R^2 in (15, 16] or
-  // (35, 36] gives the same integer cells.
-  const double R2 = (p->cutoff * p->sigma) * (p->cutoff * p->sigma);
-  c->piece_ext = (R2 > 15.0 && R2 <= 16.0) ? 3 : (R2 > 35.0 && R2 <= 36.0) ? 5 : 0;
   // A ball of extent up to 8 reaches only the tiles next to its own.
   const int ext = ball_extent(p->cutoff * p->sigma);
   c->plan_ext = (ext >= 1 && ext <= 8) ? ext : 0;
   c->pb.cap = 0;
-  if (c->piece_ext) {
+  if (c->plan_ext) {
     const int64_t N = c->N;
     const int64_t ntiles = (N / 8) * (N / 8) * (N / 8);
     const int64_t mp = max_particles > 0 ? max_particles : 1;
-    const int64_t most = max_pieces(ntiles, mp, piece_size(ext));
-    const int64_t te = 8 + 2 * c->piece_ext;
+    const int64_t most = max_pieces(ntiles, mp);
+    const int64_t te = 8 + 2 * c->plan_ext;
     const int64_t by_bytes = ((int64_t)2 << 30) / (te * te * te * 8);      // 2 GB of staging
     c->pb.cap = (int)(most < by_bytes ? most : by_bytes);
   }
@@ -276,10 +269,10 @@ static size_t carve(pm_ctx* c, Carver& cv) {
     c->pb.pc_off = cv.take<int>(ntiles + 1);
     c->pb.list_off = cv.take<int>(ntiles + 1);
     c->pb.list = cv.take<int>(ntiles);
-    c->pb.ptile = cv.take<int>((size_t)max_pieces((int64_t)ntiles, (int64_t)mp, piece_size(c->plan_ext)));
+    c->pb.ptile = cv.take<int>((size_t)max_pieces((int64_t)ntiles, (int64_t)mp));
     c->pb.counter = cv.take<int>(16);
     c->pb.tmax = cv.take<unsigned>(ntiles);
-    if (c->piece_ext) c->pb.stage = cv.take<long long>(piece_stage_cells(c->piece_ext, c->pb.cap));
+    c->pb.stage = cv.take<long long>(piece_stage_cells(c->plan_ext, c->pb.cap));
   }
   return (cv.off + 255) & ~(size_t)255;
 }
@@ -413,9 +406,8 @@ pm_status pm_create(const pm_params* p, int64_t max_particles, void* workspace, 
     const size_t te = 8 + 2 * (size_t)ext;
     c->kg.private_tiles = (4 * te * te * te * sizeof(float) <= 96 * 1024) ? 1 : 0;
   }
-  c->kg.piece_ext = c->piece_ext;
   c->kg.plan_ext = c->plan_ext;
-  c->kg.piece = piece_size(ext);
+  c->kg.piece = kMinPiece;
   c->kg.nrows = c->nrows;
   c->kg.rows = c->rowtab;
 
@@ -749,15 +741,14 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
 // Tile sort of the particles, then (tile-piece kernels) the piece plan.
 static hipError_t sort_and_plan(pm_ctx* c, const float* pos, int64_t n) {
   Timed t(c, PM_T_SORT);
-  const hipError_t e = sort_particles(c->kg, c->sb, pos, n, c->st, c->perm_n == n, c->plan_ext ? &c->pb : nullptr);
-  c->perm_n = (e == hipSuccess) ? n : -1;
-  return e;
+  c->kg.piece = piece_size(n);
+  return sort_particles(c->kg, c->sb, pos, n, c->st, c->plan_ext ? &c->pb : nullptr);
 }
 
 static hipError_t deposit_any(pm_ctx* c, const float* pos, const float* mass, int64_t n, float* rho,
                               double* s_store) {
   Timed t(c, PM_T_DEPOSIT);
-  if (c->piece_ext) return deposit_pieces(c->kg, c->sb, c->pb, pos, mass, n, rho, c->st);
+  if (c->plan_ext) return deposit_pieces(c->kg, c->sb, c->pb, pos, mass, n, rho, c->st);
   return deposit_sorted(c->kg, c->sb, pos, mass, n, rho, s_store, c->st);
 }
 

@@ -179,37 +179,36 @@ struct KernelGeom {
   int analytic;     // literal prefactor instead of the ball-sum normalisation
   double analytic_norm;  // (2 pi)^1.5 sigma^3
   int private_tiles;     // deposit: one LDS tile copy per wave (no LDS atomics)
-  int piece_ext;         // 3 or 5: the ball has a compiled shape (radius 4 at sigma 1
-                         // or 1.5) and the tile-piece deposit runs; 0: generic deposit
-  int plan_ext;          // 1..8: the tile-piece gather runs (the ball reaches no further
-                         // than the neighbouring tiles); 0: generic gather
-  int piece;             // most particles of a piece
+  int plan_ext;          // 1..8: the tile-piece kernels run (the ball reaches no further
+                         // than the neighbouring tiles); 0: generic kernels
+  int piece;             // most particles of a piece (piece_size)
   int nrows;             // rows (dy, dz) of the ball
   const int* rows;       // packed rows (dy + 16) | (dz + 16) << 8 | half-width << 16
 };
 
 struct SortBufs {
-  int* keys;        // [N] tile of each particle
+  int* keys;        // [N] tile of each particle, in the sort's processing order for the pieces
   int* rank;        // [N] rank within its tile
   int* perm;        // [N] sorted order -> particle index
-  int* skey;        // [N] tile of perm[i]
+  int* skey;        // [N] tile of perm[i] (generic kernels), or the particle of each key
   int* counts;      // [ntiles + 1]
   int* offsets;     // [ntiles + 1] exclusive scan of counts
   int* blocksums;   // scan scratch: [3][scan blocks]
   int ntiles;
-  int* flags;       // [0]: bounds violations
+  int* flags;       // [0]: bounds violations, [1]: particles perm is a permutation of (0: none)
 };
 
 // Tile pieces (pm_pieces.hip): a tile's sorted particles in runs of at most
-// piece_size(ext), each deposited into its own staging slot (slots < cap) or
-// straight into rho with atomics (slots >= cap).
-#ifndef PM_PIECE
-#define PM_PIECE 1024
-#endif
-#ifndef PM_PIECE_WIDE
-#define PM_PIECE_WIDE 128
-#endif
-inline int piece_size(int ext) { return ext <= 3 ? PM_PIECE : PM_PIECE_WIDE; }
+// piece_size(n), each deposited into its own staging slot (slots < cap) or
+// straight into rho with atomics (slots >= cap).  About a thousand pieces keep
+// every CU busy; smaller ones only add staged boxes, which the reduction sums
+// one after the other where particles crowd into few tiles.
+constexpr int kMinPiece = 128, kMaxPiece = 1024;
+inline int piece_size(int64_t n) {
+  int p = kMinPiece;
+  while (p < kMaxPiece && p < n / 1024) p *= 2;
+  return p;
+}
 struct PieceBufs {
   int* pc_off;      // [ntiles + 1] first piece of each tile (exclusive scan)
   int* list_off;    // [ntiles + 1] exclusive scan of: the tile receives staged cells
@@ -222,9 +221,7 @@ struct PieceBufs {
   int cap;
 };
 // most pieces a sort of n particles into ntiles tiles can make
-inline int64_t max_pieces(int64_t ntiles, int64_t n, int piece) {
-  return (ntiles < n ? ntiles : n) + n / piece + 1;
-}
+inline int64_t max_pieces(int64_t ntiles, int64_t n) { return (ntiles < n ? ntiles : n) + n / kMinPiece + 1; }
 // staging cells (64-bit) for cap pieces of a ball with the given extent
 size_t piece_stage_cells(int ext, int cap);
 hipError_t deposit_pieces(const KernelGeom& kg, const SortBufs& sb, const PieceBufs& pb, const float* pos,
@@ -232,12 +229,10 @@ hipError_t deposit_pieces(const KernelGeom& kg, const SortBufs& sb, const PieceB
 hipError_t gather_pieces(const KernelGeom& kg, const SortBufs& sb, const PieceBufs& pb, const float* phi,
                          float* pos, float* vel, float* acc, int64_t n, float dt_kick, float dt_drift, int mode,
                          hipStream_t st);
-// Counting sort by tile.  prev_order: sb.perm holds the previous sort's
-// permutation of these n particles (it is read as the processing order, then
-// replaced).  pb (nullable): also the piece plan of the tile-piece kernels, and
-// their work counters set to zero.
+// Counting sort by tile.  pb (nullable): also the piece plan of the tile-piece kernels, and
+// their work counters and mass maxima set to zero.
 hipError_t sort_particles(const KernelGeom& kg, const SortBufs& sb, const float* pos, int64_t n,
-                          hipStream_t st, bool prev_order = false, const PieceBufs* pb = nullptr);
+                          hipStream_t st, const PieceBufs* pb = nullptr);
 // s_store (nullable): receives each particle's kernel normalisation (FP64)
 hipError_t deposit_sorted(const KernelGeom& kg, const SortBufs& sb, const float* pos, const float* mass,
                           int64_t n, float* rho, double* s_store, hipStream_t st);

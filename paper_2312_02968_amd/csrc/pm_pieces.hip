@@ -1,13 +1,13 @@
-// Deposit (Eq. smooth) and smoothed-force gather (Eq. gi) by tile pieces,
-// one particle per lane, for the kernel balls of radius 4 sigma with
-// sigma = 1 cell (the paper's 251 cells) and sigma = 1.5 cells.
+// Deposit (Eq. smooth) and smoothed-force gather (Eq. gi) by tile pieces, for
+// every kernel ball that reaches at most 8 cells.
 //
 // Weights.  A particle at u = x / s has the central pixel c = floor(u + 1/2)
 // and the sub-pixel offset f = c - u.  Its Gaussian weight on ball cell d is
 // exp(-|d + f|^2 / (2 sigma^2)) = wx[dx] wy[dy] wz[dz], so a lane evaluates
-// 3 (2 EXT + 1) exponentials and forms the products; the ball itself (which
-// cells are in it) is fixed at compile time, so every cell's LDS address is
-// the lane's base address plus an immediate.  The normalisation S = sum_B w is
+// 3 (2 EXT + 1) exponentials and forms the products; for the balls of radius 4
+// sigma at sigma = 1, 1.5 and 2 cells which cells are in it is known at compile
+// time, so every cell's LDS address is the lane's base address plus an
+// immediate.  The normalisation S = sum_B w is
 // summed in FP64 row by row: for the row (dy, dz) of half-width h,
 // wy[dy] wz[dz] sum_{|dx| <= h} wx[dx].
 //
@@ -24,7 +24,8 @@
 //    depends on how a tile's particles fall into pieces, so the density does
 //    not depend on the order in which the particles arrive (the sort ranks
 //    them within a tile with atomics).  Pieces beyond the staging capacity
-//    add their cells with FP32 global atomics.
+//    (and particles whose mass or position is not finite) add their cells with
+//    FP32 global atomics.
 //  - Gather: a piece loads its tile plus a halo of EXT + 1 cells of phi into
 //    LDS once; each lane then sums its particle's ball with the central
 //    difference folded into the weights, g = -(1/(2 s S)) sum_e phi(c + e) W(e)
@@ -41,22 +42,19 @@ namespace pm {
 namespace {
 constexpr int kTile = 8;
 constexpr int kNT = 256;
-// Block sizes of the deposit's tile kernel and of the gather (a piece per
-// block).  Pieces average about 70 particles on the isothermal sphere, so
-// most of a block's lanes wait while the few with particles sum their balls;
-// 128-thread gather blocks keep twice as many pieces in flight per CU (the
-// gather 361 -> 320 us there), while the deposit's tile kernel, whose LDS
-// tile bounds its blocks per CU, is faster with 256 (266 against 295 us).
-#ifndef PM_DEPOSIT_NT
-#define PM_DEPOSIT_NT 256
-#endif
+// Block sizes of the deposit and of the gather (a piece per block).  Pieces
+// average about 70 particles on the isothermal sphere, so a block of the narrow
+// ball's gather is two waves, which keeps more pieces in flight per CU.
+constexpr int kDepNT = 256;
+// Particles up to which a pass goes by rows of the ball, one particle per wave,
+// and not by one particle per lane.
+constexpr int kRowMost = 16;
 #ifndef PM_GATHER_NT
 #define PM_GATHER_NT 128
 #endif
 #ifndef PM_GATHER_NT_WIDE
 #define PM_GATHER_NT_WIDE 256
 #endif
-constexpr int kDepNT = PM_DEPOSIT_NT;
 constexpr int gather_nt(int ext) { return ext <= 3 ? PM_GATHER_NT : PM_GATHER_NT_WIDE; }
 
 __device__ __forceinline__ int wrapi(int i, int N) { return i & (N - 1); }
@@ -86,13 +84,11 @@ template <int EXT>
 struct Lane {
   int cx, cy, cz;              // central pixel (wrapped grid index)
   float wx[2 * EXT + 1], wy[2 * EXT + 1], wz[2 * EXT + 1];
-  double S;                    // FP64 ball sum of the weights
   double sx[EXT + 1];          // sum of wx over |dx| <= h
 };
 
-template <int EXT, int R2>
-__device__ __forceinline__ void lane_setup(Lane<EXT>& L, const KernelGeom& kg, float px, float py, float pz,
-                                           bool with_sum) {
+template <int EXT>
+__device__ __forceinline__ void lane_setup(Lane<EXT>& L, const KernelGeom& kg, float px, float py, float pz) {
   const int half = kg.N / 2;
   float fx, fy, fz;
   L.cx = wrapi(central_pixel(px, kg.inv_s, &fx) + half, kg.N);
@@ -105,21 +101,9 @@ __device__ __forceinline__ void lane_setup(Lane<EXT>& L, const KernelGeom& kg, f
     L.wy[d + EXT] = expf(-ey * ey * kg.inv2sig2);
     L.wz[d + EXT] = expf(-ez * ez * kg.inv2sig2);
   }
-  L.S = 0.0;
   L.sx[0] = (double)L.wx[EXT];
 #pragma unroll
   for (int h = 1; h <= EXT; ++h) L.sx[h] = L.sx[h - 1] + ((double)L.wx[EXT - h] + (double)L.wx[EXT + h]);
-  if (!with_sum) return;
-  double S = 0.0;
-  static_for<-EXT, EXT + 1>([&](auto DZc) {
-    constexpr int dz = decltype(DZc)::value;
-    static_for<-EXT, EXT + 1>([&](auto DYc) {
-      constexpr int dy = decltype(DYc)::value;
-      constexpr int h = row_half(dy, dz, R2, EXT);
-      if constexpr (h >= 0) S += (double)L.wy[dy + EXT] * (double)L.wz[dz + EXT] * L.sx[h];
-    });
-  });
-  L.S = S;
 }
 
 // Blocks take pieces from a work counter (pieces differ in size by three
@@ -132,20 +116,119 @@ __device__ __forceinline__ int next_piece(int* counter, int* slot) {
 }
 
 // ---------------------------------------------------------------------------
+// weights of a batch of particles
+// ---------------------------------------------------------------------------
+// Weights of up to NT / 4 particles into w[p][3 W] (x, y, z), four threads per
+// particle, and their normalisations into norm[p].  index(p): the particle of
+// batch entry p.  base[p]: its central cell in the LDS tile (row pitch RP, plane
+// pitch PP, halo HE).  Ends with a barrier.
+template <int EXT, int NT, typename T, typename F>
+__device__ __forceinline__ void weights_to_lds(const KernelGeom& kg, const float* __restrict__ pos, int count, int HE,
+                                               int RP, int PP, const int* hrow, T* w, double* norm, int* base,
+                                               F&& index) {
+  constexpr int W = 2 * EXT + 1, WS = 3 * W + 1;
+  const int p = threadIdx.x >> 2, q = threadIdx.x & 3;
+  const bool on = p < count;
+  T* wp = w + p * WS;
+  if (on) {
+    const int64_t i = index(p);
+    const int half = kg.N / 2;
+    float f[3];
+    int c[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      c[a] = wrapi(central_pixel(pos[3 * i + a], kg.inv_s, &f[a]) + half, kg.N) & (kTile - 1);
+    for (int d = q; d < 3 * W; d += 4) {
+      const int a = d / W;
+      const float e = (float)(d - a * W - EXT) + (a == 0 ? f[0] : a == 1 ? f[1] : f[2]);
+      wp[d] = (T)expf(-e * e * kg.inv2sig2);
+    }
+    if (q == 0) base[p] = (c[2] + HE) * PP + (c[1] + HE) * RP + c[0] + HE;
+  }
+  __syncthreads();
+  double S = 0.0;
+  if (on && !kg.analytic) {
+    // sum over the ball, row by row: wy wz sum_{|dx| <= h} wx in FP64
+    double sx[EXT + 1];
+    sx[0] = (double)wp[EXT];
+#pragma unroll
+    for (int h = 1; h <= EXT; ++h) sx[h] = sx[h - 1] + ((double)wp[EXT - h] + (double)wp[EXT + h]);
+    for (int z = q; z < W; z += 4) {
+      double t = 0.0;
+      for (int y = 0; y < W; ++y) {
+        const int h = hrow[z * W + y];
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k <= EXT; ++k) v = (h == k) ? sx[k] : v;
+        t = fma((double)wp[W + y], v, t);
+      }
+      S = fma((double)wp[2 * W + z], t, S);
+    }
+  }
+  S += __shfl_xor(S, 1, 64);
+  S += __shfl_xor(S, 2, 64);
+  if (on && q == 0) norm[p] = kg.analytic ? kg.analytic_norm : S;
+  __syncthreads();
+}
+
+// The ball's rows from the context's table: half-widths by (dz, dy) into
+// hrow[W][W] (-1: no row; block-wide, no barrier at the end), and the lane's own
+// rows lane + 64 u.
+template <int EXT, int RU>
+__device__ __forceinline__ void ball_rows(const KernelGeom& kg, int NT, int RP, int PP, int* hrow, int* roff, int* rh,
+                                          int* ry, int* rz) {
+  constexpr int W = 2 * EXT + 1;
+  for (int j = threadIdx.x; j < W * W; j += NT) hrow[j] = -1;
+  __syncthreads();
+  for (int j = threadIdx.x; j < kg.nrows; j += NT) {
+    const int r = kg.rows[j];
+    hrow[(((r >> 8) & 255) - 16 + EXT) * W + (r & 255) - 16 + EXT] = r >> 16;
+  }
+#pragma unroll
+  for (int u = 0; u < RU; ++u) {
+    const int k = (threadIdx.x & 63) + 64 * u;
+    const int r = k < kg.nrows ? kg.rows[k] : (16 | 16 << 8);
+    ry[u] = (r & 255) - 16;
+    rz[u] = ((r >> 8) & 255) - 16;
+    rh[u] = k < kg.nrows ? r >> 16 : -1;
+    roff[u] = rz[u] * PP + ry[u] * RP;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // deposit
 // ---------------------------------------------------------------------------
-// Fixed-point cell sums.  LDS adds of 64-bit integers are native and an
-// order of magnitude faster than LDS adds of FP32 on this chip (those take a
-// slow path), and integer sums are exact, so a piece accumulates its balls as
-// integers: each contribution c (FP32) becomes round(c 2^k) with one
-// power-of-two scale per tile, shared by the tile's pieces, chosen so that
-// no cell sum over all the tile's particles can overflow; the cell's FP32
-// value is the integer sum times 2^-k.  The product of the three normalised
-// 1D weights is at most 1, so every contribution of particle i is at most
-// A_i = |m_i| / (S_i s^3) <= |m_i| / (w0 s^3), w0 being the smallest possible
-// central-cell weight; a tile of n_t particles adds at most n_t contributions
-// to a cell.  With A < 2^e for the tile's largest |m|, k = 61 - ceil(log2 n_t)
-// - e keeps every sum below 2^61.
+// Fixed-point cell sums.  LDS adds of 64-bit integers are native and an order
+// of magnitude faster than LDS adds of FP32 on this chip (those take a slow
+// path), and integer sums are exact, so a piece accumulates its balls as
+// integers: each contribution c becomes round(c 2^k) with one power-of-two
+// scale per tile, shared by the tile's pieces, chosen so that no cell sum over
+// all the tile's particles can overflow; the cell's FP32 value is the integer
+// sum times 2^-k.  The product of the three normalised 1D weights is at most 1,
+// so every contribution of particle i is at most A_i = |m_i| / (S_i s^3) <=
+// |m_i| / (w0 s^3), w0 being the smallest possible central-cell weight; a tile of
+// n_t particles adds at most n_t contributions to a cell.  With A < 2^e for the
+// tile's largest |m|, k = 51 - ceil(log2 n_t) - e keeps every sum below 2^51,
+// where round(c 2^k) is the low part of the FP64 number c 2^k + 3 2^51: one
+// multiply-add makes it from the weights.
+//
+// Work split.  The piece's particles are ordered by cell and go in batches of
+// 64, whose weights four threads per particle put into LDS.
+//  - By rows: lanes own rows (dy, dz) of the ball and a wave takes one particle
+//    at a time, so a wave's adds go to distinct cells however the particles
+//    crowd; a lane keeps its row's sums in registers, with LDS adds only when
+//    the cell changes.  Three instructions per dx and lane.
+//  - One particle per lane (the 251 cells of radius 4, batches of more than
+//    kRowMost particles): the ball's slices dz are dealt to the four waves, two
+//    instructions and an LDS add per cell at compile-time offsets.  Neighbouring
+//    lanes take particles far apart in the cell order, so that few of a wave's
+//    adds meet at one address.
+// Bound: vector instructions by rows, LDS adds by lanes.  Measured, tile kernel:
+// the ring's 4097 particles (sigma = 1.5) 48 us, 425 us with a lane per particle
+// in the sort's order, whose adds ran up to 64 deep on one address; 300 001
+// particles of a mixture (sigma = 1) 103 us, 134 us that way, 126 us all by
+// rows; the isothermal sphere's 2^20, about 70 to a piece, 302 us (265 us with
+// each wave taking particles of its own and no ordering).
 __device__ __forceinline__ int tile_scale_exp(const KernelGeom& kg, unsigned mbits, int count) {
   const double s3 = (double)kg.s * kg.s * kg.s;
   // the normalisation is at least the central cell's weight, whose offset is
@@ -155,11 +238,12 @@ __device__ __forceinline__ int tile_scale_exp(const KernelGeom& kg, unsigned mbi
   int e = 0;
   frexp(A > 0.0 ? A : 1.0, &e);                   // A < 2^e
   const int cb = count > 1 ? 32 - __clz(count - 1) : 0;      // ceil(log2 count)
-  return 61 - cb - e;
+  return 51 - cb - e;
 }
 
 // Largest |m| of each tile's particles, tmax[t] (float bits; zeroed before),
 // from the pieces: a block reduces a piece and adds one atomic max per wave.
+// Values that are not finite set no scale.
 __global__ __launch_bounds__(kNT) void k_tile_mass_max(const int* __restrict__ perm, const int* __restrict__ offsets,
                                                       const int* __restrict__ pc_off, const int* __restrict__ ptile,
                                                       int ntiles, int piece, const float* __restrict__ mass,
@@ -170,105 +254,205 @@ __global__ __launch_bounds__(kNT) void k_tile_mass_max(const int* __restrict__ p
     const int a = offsets[t] + (p - pc_off[t]) * piece;
     const int b = min(a + piece, offsets[t + 1]);
     float m = 0.0f;
-    for (int j = a + (int)threadIdx.x; j < b; j += kNT) m = fmaxf(m, fabsf(mass[perm[j]]));
+    for (int j = a + (int)threadIdx.x; j < b; j += kNT) {
+      const float v = fabsf(mass[perm[j]]);
+      m = v < INFINITY ? fmaxf(m, v) : m;
+    }
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     if ((threadIdx.x & 63) == 0 && m > 0.0f) atomicMax(&tmax[t], __float_as_uint(m));   // non-negative floats order as their bits
   }
 }
-__device__ __forceinline__ unsigned long long to_fixed(float c, int k) {
-  const float t = ldexpf(fabsf(c), k);                  // < 2^61 by the choice of k
-  const unsigned hi = (unsigned)(t * 2.3283064365386963e-10f);   // t / 2^32, truncated
-  const unsigned lo = (unsigned)fmaf(-(float)hi, 4294967296.0f, t);
-  const unsigned long long u = ((unsigned long long)hi << 32) | lo;
-  return c < 0.0f ? (unsigned long long)(-(long long)u) : u;
-}
 
+constexpr double kFixMagic = 6755399441055744.0;           // 3 2^51
+constexpr unsigned kFixMagicHi = 0x43380000u;               // its high word; the low word is 0
+
+// Pitches of the deposit's LDS tile: odd, so that a wave's rows spread over
+// the banks.
+template <int EXT>
+struct DepTile {
+  static constexpr int TE = kTile + 2 * EXT, RP = TE | 1, PP = RP * TE + 2;
+  static constexpr size_t cells = (size_t)PP * TE;
+};
+constexpr int kDepBatch = kDepNT / 4;
+
+// R2: the compiled shape of the lane path, 0 without one.
 template <int EXT, int R2>
 __global__ __launch_bounds__(kDepNT) void k_deposit_pieces(KernelGeom kg, const int* __restrict__ perm,
-                                                        const int* __restrict__ offsets,
-                                                        const int* __restrict__ pc_off,
-                                                        const int* __restrict__ ptile, int ntiles, int piece,
-                                                        int* counter, const float* __restrict__ pos,
-                                                        const float* __restrict__ mass,
-                                                        const unsigned* __restrict__ tmax, long long* stage, int cap,
-                                                        float* rho) {
-  constexpr int TE = kTile + 2 * EXT;
-  constexpr int TE3 = TE * TE * TE;
-  extern __shared__ unsigned long long tile64[];   // TE^3 fixed-point cell sums
-  const int N = kg.N, nt = N / kTile;
+                                                           const int* __restrict__ offsets,
+                                                           const int* __restrict__ pc_off,
+                                                           const int* __restrict__ ptile, int ntiles, int* counter,
+                                                           const float* __restrict__ pos,
+                                                           const float* __restrict__ mass,
+                                                           const unsigned* __restrict__ tmax, long long* stage,
+                                                           int cap, float* rho) {
+  using D = DepTile<EXT>;
+  constexpr int TE = D::TE, RP = D::RP, PP = D::PP, TE3 = TE * TE * TE;
+  constexpr int W = 2 * EXT + 1, WS = 3 * W + 1, RU = (W * W + 63) / 64;
+  extern __shared__ unsigned long long tile64[];
+  double* wb = reinterpret_cast<double*>(tile64 + D::cells);      // [kDepBatch][WS]
+  __shared__ double norm[kDepBatch], amp[kDepBatch];
+  __shared__ int cell[kDepBatch], bins[512], wsum[kDepNT / 64];
+  __shared__ unsigned short order[kMaxPiece];
+  __shared__ int hrow[W * W];
+  __shared__ int slot;
+  const int N = kg.N, nt = N / kTile, piece = kg.piece;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double s3 = (double)kg.s * kg.s * kg.s;
   const int total = pc_off[ntiles];
-  __shared__ int slot;
+  int roff[RU], rh[RU], ry[RU], rz[RU];
+  ball_rows<EXT, RU>(kg, kDepNT, RP, PP, hrow, roff, rh, ry, rz);
   for (int p = next_piece(counter, &slot); p < total; p = next_piece(counter, &slot)) {
     const int t = ptile[p];
     const int a = offsets[t] + (p - pc_off[t]) * piece;
-    const int b = min(a + piece, offsets[t + 1]);
+    const int n = min(piece, offsets[t + 1] - a);
     const int tx = t % nt, ty = (t / nt) % nt, tz = t / (nt * nt);
-    const int ox = tx * kTile - EXT, oy = ty * kTile - EXT, oz = tz * kTile - EXT;
     const bool staged = p < cap;
-    int k = 0;
-    if (staged) {
-      for (int j = threadIdx.x; j < TE3; j += kDepNT) tile64[j] = 0ull;
+    const int k = staged ? tile_scale_exp(kg, tmax[t], offsets[t + 1] - offsets[t]) : 0;
+    // particles in the order of their cells (few particles: as they come)
+    const bool sorted = n > 32;
+    for (int j = threadIdx.x; j < (int)D::cells; j += kDepNT) tile64[j] = 0ull;
+    if (sorted) {
+      bins[threadIdx.x] = bins[threadIdx.x + 256] = 0;
       __syncthreads();
-      k = tile_scale_exp(kg, tmax[t], offsets[t + 1] - offsets[t]);
-    }
-    for (int j = a + (int)threadIdx.x; j < b; j += kDepNT) {
-      const int64_t i = perm[j];
-      Lane<EXT> L;
-      lane_setup<EXT, R2>(L, kg, pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], !kg.analytic);
-      const double norm = kg.analytic ? kg.analytic_norm : L.S;
-      const float scale = (float)((double)mass[i] / (norm * s3));
-      if (staged) {
-        // the ball's corner cell in the tile; every cell is an immediate offset
-        const int lx = wrapi(L.cx - ox, N), ly = wrapi(L.cy - oy, N), lz = wrapi(L.cz - oz, N);
-        unsigned long long* base = tile64 + ((lz - EXT) * TE + (ly - EXT)) * TE + (lx - EXT);
-        static_for<-EXT, EXT + 1>([&](auto DZc) {
-          constexpr int dz = decltype(DZc)::value;
-          static_for<-EXT, EXT + 1>([&](auto DYc) {
-            constexpr int dy = decltype(DYc)::value;
-            constexpr int h = row_half(dy, dz, R2, EXT);
-            if constexpr (h >= 0) {
-              const float ayz = scale * L.wy[dy + EXT] * L.wz[dz + EXT];
-              static_for<-h, h + 1>([&](auto DXc) {
-                constexpr int dx = decltype(DXc)::value;
-                constexpr int off = ((dz + EXT) * TE + (dy + EXT)) * TE + (dx + EXT);
-                __hip_atomic_fetch_add(base + off, to_fixed(ayz * L.wx[dx + EXT], k), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-              });
-            }
-          });
-        });
-      } else {
-        static_for<-EXT, EXT + 1>([&](auto DZc) {
-          constexpr int dz = decltype(DZc)::value;
-          static_for<-EXT, EXT + 1>([&](auto DYc) {
-            constexpr int dy = decltype(DYc)::value;
-            constexpr int h = row_half(dy, dz, R2, EXT);
-            if constexpr (h >= 0) {
-              const float ayz = scale * L.wy[dy + EXT] * L.wz[dz + EXT];
-              const long long r = ((long long)wrapi(L.cz + dz, N) * N + wrapi(L.cy + dy, N)) * N;
-              static_for<-h, h + 1>([&](auto DXc) {
-                constexpr int dx = decltype(DXc)::value;
-                unsafeAtomicAdd(&rho[r + wrapi(L.cx + dx, N)], ayz * L.wx[dx + EXT]);
-              });
-            }
-          });
-        });
+      int key[kMaxPiece / kDepNT], rank[kMaxPiece / kDepNT];
+#pragma unroll
+      for (int u = 0; u < kMaxPiece / kDepNT; ++u) {
+        const int j = threadIdx.x + u * kDepNT;
+        if (j < n) {
+          const int64_t i = perm[a + j];
+          int c[3];
+          for (int x = 0; x < 3; ++x)
+            c[x] = (central_pixel(pos[3 * i + x], kg.inv_s, nullptr) + N / 2) & (kTile - 1);
+          key[u] = (c[2] * kTile + c[1]) * kTile + c[0];
+          rank[u] = atomicAdd(&bins[key[u]], 1);
+        }
+      }
+      __syncthreads();
+      const int b0 = bins[2 * threadIdx.x], b1 = bins[2 * threadIdx.x + 1];
+      int x = b0 + b1;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+      }
+      if (lane == 63) wsum[wave] = x;
+      __syncthreads();
+      for (int w = 0; w < wave; ++w) x += wsum[w];
+      bins[2 * threadIdx.x] = x - b0 - b1;
+      bins[2 * threadIdx.x + 1] = x - b1;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kMaxPiece / kDepNT; ++u) {
+        const int j = threadIdx.x + u * kDepNT;
+        if (j < n) order[bins[key[u]] + rank[u]] = (unsigned short)j;
       }
     }
-    if (staged) {
+    __syncthreads();
+    for (int j0 = 0; j0 < n; j0 += kDepBatch) {
+      const int count = min(kDepBatch, n - j0);
+      // (by lanes, entry q of batch b is the particle q nb + b of the cell order)
+      const int nb = n / kDepBatch, b = j0 / kDepBatch;
+      const bool spread = R2 > 0 && b < nb;
+      auto at = [&](int q) { return perm[a + (sorted ? (int)order[spread ? q * nb + b : j0 + q] : j0 + q)]; };
+      weights_to_lds<EXT, kDepNT>(kg, pos, count, EXT, RP, PP, hrow, wb, norm, cell, at);
+      if (threadIdx.x < count) amp[threadIdx.x] = ldexp((double)mass[at(threadIdx.x)] / (norm[threadIdx.x] * s3), k);
       __syncthreads();
+      if constexpr (R2 > 0) {
+        bool lanes = staged && count > kRowMost;
+        for (int q = 0; q < count && lanes; q += 64) lanes = __all(q + lane >= count || fabs(amp[q + lane]) < INFINITY);
+        if (lanes) {
+          if (lane < count) {
+            const double* wp = wb + lane * WS;
+            const double m = amp[lane];
+            double wx[W];
+#pragma unroll
+            for (int d = 0; d < W; ++d) wx[d] = wp[d];
+            unsigned long long* c0 = tile64 + cell[lane];
+            static_for<-EXT, EXT + 1>([&](auto DZc) {
+              constexpr int dz = decltype(DZc)::value;
+              if ((dz + EXT) % (kDepNT / 64) != wave) return;
+              const double mz = m * wp[2 * W + dz + EXT];
+              static_for<-EXT, EXT + 1>([&](auto DYc) {
+                constexpr int dy = decltype(DYc)::value;
+                constexpr int h = row_half(dy, dz, R2, EXT);
+                if constexpr (h >= 0) {
+                  const double ayz = mz * wp[W + dy + EXT];
+                  static_for<-h, h + 1>([&](auto DXc) {
+                    constexpr int dx = decltype(DXc)::value;
+                    const unsigned long long v = (unsigned long long)__double_as_longlong(fma(ayz, wx[dx + EXT], kFixMagic)) -
+                                                 ((unsigned long long)kFixMagicHi << 32);
+                    __hip_atomic_fetch_add(c0 + dz * PP + dy * RP + dx, v, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                  });
+                }
+              });
+            });
+          }
+          __syncthreads();
+          continue;
+        }
+      }
+      // a run of the batch per wave
+      const int per = (count + kDepNT / 64 - 1) / (kDepNT / 64);
+      const int q0 = wave * per, q1 = min(q0 + per, count);
+#pragma unroll 1
+      for (int u = 0; u < RU; ++u) {
+        if (64 * u >= kg.nrows) break;
+        const int h = rh[u], yo = W + ry[u] + EXT, zo = 2 * W + rz[u] + EXT;
+        unsigned long long acc[W];
+        int run = 0, cur = -1;
+        auto flush = [&]() {
+          if (run == 0) return;
+          unsigned long long* c0 = tile64 + cur + roff[u];
+          const unsigned long long off = (unsigned long long)(kFixMagicHi * (unsigned)run) << 32;
+#pragma unroll
+          for (int d = -EXT; d <= EXT; ++d)
+            if ((d < 0 ? -d : d) <= h)
+              __hip_atomic_fetch_add(c0 + d, acc[d + EXT] - off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          run = 0;
+        };
+        for (int q = q0; q < q1; ++q) {
+          const double* wp = wb + q * WS;
+          const double m = amp[q];
+          const int c = __builtin_amdgcn_readfirstlane(cell[q]);
+          if (staged && fabs(m) < INFINITY) {
+            if (c != cur || run == 0) {
+              flush();
+              cur = c;
+#pragma unroll
+              for (int d = 0; d < W; ++d) acc[d] = 0ull;
+            }
+            const double ayz = m * wp[yo] * wp[zo];
+#pragma unroll
+            for (int d = 0; d < W; ++d)
+              acc[d] += (unsigned long long)__double_as_longlong(fma(ayz, wp[d], kFixMagic));
+            ++run;
+          } else if (h >= 0) {
+            // no staging slot left (or a value that is not finite): FP32 adds to rho
+            const double ayz = ldexp(m, -k) * wp[yo] * wp[zo];
+            const int lz = c / PP, ly = (c - lz * PP) / RP, lx = c - lz * PP - ly * RP;
+            const long long r = ((long long)wrapi(tz * kTile + lz - EXT + rz[u], N) * N +
+                                 wrapi(ty * kTile + ly - EXT + ry[u], N)) * N;
+            for (int d = -h; d <= h; ++d)
+              unsafeAtomicAdd(&rho[r + wrapi(tx * kTile + lx - EXT + d, N)], (float)(ayz * wp[d + EXT]));
+          }
+        }
+        flush();
+      }
+      __syncthreads();
+    }
+    if (staged) {
       // a tile of several pieces stages integers, summed exactly by the
       // reduction; a lone piece's box is already its tile's exact sum and is
       // staged as FP32 (the slot's first half), half the bytes
-      if (pc_off[t + 1] - pc_off[t] > 1) {
-        long long* dst = stage + (size_t)p * TE3;
-        for (int j = threadIdx.x; j < TE3; j += kDepNT) dst[j] = (long long)tile64[j];
-      } else {
-        float* dst = reinterpret_cast<float*>(stage + (size_t)p * TE3);
-        for (int j = threadIdx.x; j < TE3; j += kDepNT) dst[j] = (float)ldexp((double)(long long)tile64[j], -k);
+      const bool multi = pc_off[t + 1] - pc_off[t] > 1;
+      long long* dst = stage + (size_t)p * TE3;
+      float* dstf = reinterpret_cast<float*>(dst);
+      for (int j = threadIdx.x; j < TE3; j += kDepNT) {
+        const int lx = j % TE, ly = (j / TE) % TE, lz = j / (TE * TE);
+        const long long v = (long long)tile64[lz * PP + ly * RP + lx];
+        if (multi) dst[j] = v;
+        else dstf[j] = (float)ldexp((double)v, -k);
       }
-      __syncthreads();
     }
   }
 }
@@ -394,63 +578,6 @@ __global__ __launch_bounds__(kRedNT) void k_deposit_reduce(KernelGeom kg, const 
 // smooth_accel call takes 134 us, 3000 us with one wave per particle reading
 // six neighbours per cell from memory; the ring (4097 particles, sigma = 1.5)
 // gathers and pushes in 40 us instead of 115 with a lane per particle alone.
-constexpr int kRowMost = 16;
-
-// Weights of up to NT / 4 particles (sorted order j0 ..) into w[p][3 W] (x, y, z),
-// four threads per particle, and their normalisations into norm[p].  base[p]:
-// the particle's central cell in the LDS tile (row pitch RP, plane pitch PP,
-// halo HE).  Ends with a barrier.
-template <int EXT, int NT>
-__device__ __forceinline__ void weights_to_lds(const KernelGeom& kg, const int* __restrict__ perm,
-                                               const float* __restrict__ pos, int j0, int count, int HE, int RP, int PP,
-                                               const int* hrow, float* w, double* norm, int* base, int* index) {
-  constexpr int W = 2 * EXT + 1, WS = 3 * W + 1;
-  const int p = threadIdx.x >> 2, q = threadIdx.x & 3;
-  const bool on = p < count;
-  float* wp = w + p * WS;
-  if (on) {
-    const int i = perm[j0 + p];
-    const int half = kg.N / 2;
-    float f[3];
-    int c[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-      c[a] = wrapi(central_pixel(pos[3 * (int64_t)i + a], kg.inv_s, &f[a]) + half, kg.N) & (kTile - 1);
-    for (int d = q; d < 3 * W; d += 4) {
-      const int a = d / W;
-      const float e = (float)(d - a * W - EXT) + (a == 0 ? f[0] : a == 1 ? f[1] : f[2]);
-      wp[d] = expf(-e * e * kg.inv2sig2);
-    }
-    if (q == 0) {
-      base[p] = (c[2] + HE) * PP + (c[1] + HE) * RP + c[0] + HE;
-      index[p] = i;
-    }
-  }
-  __syncthreads();
-  double S = 0.0;
-  if (on && !kg.analytic) {
-    // sum over the ball, row by row: wy wz sum_{|dx| <= h} wx in FP64
-    double sx[EXT + 1];
-    sx[0] = (double)wp[EXT];
-#pragma unroll
-    for (int h = 1; h <= EXT; ++h) sx[h] = sx[h - 1] + ((double)wp[EXT - h] + (double)wp[EXT + h]);
-    for (int z = q; z < W; z += 4) {
-      double t = 0.0;
-      for (int y = 0; y < W; ++y) {
-        const int h = hrow[z * W + y];
-        double v = 0.0;
-#pragma unroll
-        for (int k = 0; k <= EXT; ++k) v = (h == k) ? sx[k] : v;
-        t = fma((double)wp[W + y], v, t);
-      }
-      S = fma((double)wp[2 * W + z], t, S);
-    }
-  }
-  S += __shfl_xor(S, 1, 64);
-  S += __shfl_xor(S, 2, 64);
-  if (on && q == 0) norm[p] = kg.analytic ? kg.analytic_norm : S;
-  __syncthreads();
-}
 
 // Acceleration from the summed differences, then the store or the push.
 __device__ __forceinline__ void gather_out(const KernelGeom& kg, int64_t i, double norm, float gx, float gy, float gz,
@@ -592,28 +719,14 @@ __global__ __launch_bounds__(gather_nt(EXT)) void k_gather_pieces(KernelGeom kg,
   float* wbuf = reinterpret_cast<float*>(gsm);     // [kRowBatch][WS] weights of the row pass
   float* tile = reinterpret_cast<float*>(gsm) + gather_scratch<EXT>();
   __shared__ double norm[kRowBatch];
-  __shared__ int cell[kRowBatch], index[kRowBatch];
+  __shared__ int cell[kRowBatch];
   __shared__ int hrow[W * W];
   __shared__ int slot;
   const int N = kg.N, nt = N / kTile;
   const int total = pc_off[ntiles];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int j = threadIdx.x; j < W * W; j += kGatNT) hrow[j] = -1;
-  __syncthreads();
-  for (int j = threadIdx.x; j < kg.nrows; j += kGatNT) {
-    const int r = kg.rows[j];
-    hrow[(((r >> 8) & 255) - 16 + EXT) * W + (r & 255) - 16 + EXT] = r >> 16;
-  }
   int roff[RU], rh[RU], ry[RU], rz[RU];
-#pragma unroll
-  for (int u = 0; u < RU; ++u) {
-    const int k = lane + 64 * u;
-    const int r = k < kg.nrows ? kg.rows[k] : (16 | 16 << 8);
-    ry[u] = (r & 255) - 16;
-    rz[u] = ((r >> 8) & 255) - 16;
-    rh[u] = k < kg.nrows ? r >> 16 : -1;
-    roff[u] = rz[u] * PP + ry[u] * RP;
-  }
+  ball_rows<EXT, RU>(kg, kGatNT, RP, PP, hrow, roff, rh, ry, rz);
   for (int p = next_piece(counter, &slot); p < total; p = next_piece(counter, &slot)) {
     const int t = ptile[p];
     const int a = offsets[t] + (p - pc_off[t]) * piece;
@@ -634,7 +747,7 @@ __global__ __launch_bounds__(gather_nt(EXT)) void k_gather_pieces(KernelGeom kg,
       for (int j0 = a; j0 < mid; j0 += 64) {
         const int64_t i = perm[min(j0 + lane, mid - 1)];
         Lane<EXT> L;
-        lane_setup<EXT, R2>(L, kg, pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], false);
+        lane_setup<EXT>(L, kg, pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]);
         const int lx = (L.cx & (kTile - 1)) + HE, ly = (L.cy & (kTile - 1)) + HE, lz = (L.cz & (kTile - 1)) + HE;
         double g[4];
         lane_gather<EXT, R2, RP, PP, NW>(L, tile + lz * PP + ly * RP + lx, wave, g);
@@ -653,7 +766,7 @@ __global__ __launch_bounds__(gather_nt(EXT)) void k_gather_pieces(KernelGeom kg,
     }
     for (int j0 = mid; j0 < b; j0 += kRowBatch) {
       const int count = min(kRowBatch, b - j0);
-      weights_to_lds<EXT, kGatNT>(kg, perm, pos, j0, count, HE, RP, PP, hrow, wbuf, norm, cell, index);
+      weights_to_lds<EXT, kGatNT>(kg, pos, count, HE, RP, PP, hrow, wbuf, norm, cell, [&](int q) { return perm[j0 + q]; });
       for (int k = wave; k < count; k += kGatNT / 64) {
         const float* wp = wbuf + k * WS;
         const float* c0 = tile + cell[k];
@@ -684,7 +797,7 @@ __global__ __launch_bounds__(gather_nt(EXT)) void k_gather_pieces(KernelGeom kg,
           gy += __shfl_xor(gy, o, 64);
           gz += __shfl_xor(gz, o, 64);
         }
-        if (lane == 0) gather_out(kg, index[k], norm[k], gx, gy, gz, pos, vel, acc, dt_kick, dt_drift, mode);
+        if (lane == 0) gather_out(kg, perm[j0 + k], norm[k], gx, gy, gz, pos, vel, acc, dt_kick, dt_drift, mode);
       }
       __syncthreads();
     }
@@ -697,7 +810,7 @@ constexpr int kPersistBlocks = 2048;
 
 template <int EXT>
 static constexpr size_t deposit_lds() {
-  return sizeof(unsigned long long) * (size_t)(kTile + 2 * EXT) * (kTile + 2 * EXT) * (kTile + 2 * EXT);
+  return sizeof(double) * (DepTile<EXT>::cells + (size_t)kDepBatch * (3 * (2 * EXT + 1) + 1));
 }
 template <int EXT>
 static constexpr size_t gather_lds() {
@@ -713,34 +826,30 @@ size_t piece_stage_cells(int ext, int cap) {
 hipError_t deposit_pieces(const KernelGeom& kg, const SortBufs& sb, const PieceBufs& pb, const float* pos,
                           const float* mass, int64_t n, float* rho, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipError_t e = hipSuccess;
+  if (kg.piece > kMaxPiece) return hipErrorInvalidValue;
   const int nt = kg.N / kTile;
-  // the tiles' fixed-point scales: their largest |m|
   hipLaunchKernelGGL(k_tile_mass_max, dim3(kPersistBlocks), dim3(kNT), 0, st, sb.perm, sb.offsets, pb.pc_off, pb.ptile,
                      sb.ntiles, kg.piece, mass, pb.tmax);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  switch (kg.piece_ext) {
+#define DEPOSIT(EXT, R2)                                                                                            \
+  hipLaunchKernelGGL((k_deposit_pieces<EXT, R2>), dim3(kPersistBlocks), dim3(kDepNT), deposit_lds<EXT>(), st, kg,      \
+                     sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, pb.counter, pos, mass, pb.tmax, pb.stage, \
+                     pb.cap, rho);                                                                                 \
+  hipLaunchKernelGGL((k_deposit_reduce<EXT>), dim3(kPersistBlocks), dim3(kRedNT), 0, st, kg, pb.list,              \
+                     pb.list_off + sb.ntiles, sb.offsets, pb.pc_off, pb.tmax, nt, kg.N, pb.stage, pb.cap, rho)
+  switch (kg.plan_ext) {
+    case 1: DEPOSIT(1, 0); break;
+    case 2: DEPOSIT(2, 0); break;
     case 3:
-      hipLaunchKernelGGL((k_deposit_pieces<3, 16>), dim3(kPersistBlocks), dim3(kDepNT), deposit_lds<3>(), st, kg,
-                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kg.piece, pb.counter, pos, mass, pb.tmax,
-                         pb.stage, pb.cap, rho);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      hipLaunchKernelGGL((k_deposit_reduce<3>), dim3(kPersistBlocks), dim3(kRedNT), 0, st, kg, pb.list,
-                         pb.list_off + sb.ntiles, sb.offsets, pb.pc_off, pb.tmax, nt, kg.N, pb.stage, pb.cap,
-                         rho);
+      if (kg.nball == 251) { DEPOSIT(3, 16); } else { DEPOSIT(3, 0); }
       break;
-    case 5:
-      hipLaunchKernelGGL((k_deposit_pieces<5, 36>), dim3(kPersistBlocks), dim3(kDepNT), deposit_lds<5>(), st, kg,
-                         sb.perm, sb.offsets, pb.pc_off, pb.ptile, sb.ntiles, kg.piece, pb.counter, pos, mass, pb.tmax,
-                         pb.stage, pb.cap, rho);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      hipLaunchKernelGGL((k_deposit_reduce<5>), dim3(kPersistBlocks), dim3(kRedNT), 0, st, kg, pb.list,
-                         pb.list_off + sb.ntiles, sb.offsets, pb.pc_off, pb.tmax, nt, kg.N, pb.stage, pb.cap,
-                         rho);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case 4: DEPOSIT(4, 0); break;
+    case 5: DEPOSIT(5, 0); break;
+    case 6: DEPOSIT(6, 0); break;
+    case 7: DEPOSIT(7, 0); break;
+    case 8: DEPOSIT(8, 0); break;
+    default: return hipErrorInvalidValue;
   }
+#undef DEPOSIT
   return hipGetLastError();
 }
 

@@ -58,3 +58,48 @@ def test_gather_smallest_box_with_a_wide_ball(M):
     ref = orc.smooth_accel(oparams(p), phi32.astype(np.float64), pos.astype(np.float64))
     assert rel_max(host(acc), ref) < 1e-6
     ctx.close()
+
+
+# Each cell is an exact fixed-point sum per neighbouring tile, rounded to FP32
+# once per tile (27 of them) and added in FP32: 27 roundings of the largest cell
+# would be 1.6e-6; the sums of 27 terms whose largest dominates stay below 1e-6.
+@pytest.mark.parametrize("sigma", [0.5, 0.75, 1.0, 1.25, 1.5, 1.75, 2.0, 2.25])
+@pytest.mark.parametrize("count", [1, 32, 33, 64, 65, 129, 1500])
+def test_deposit_balls_and_pieces(M, sigma, count):
+    print("deposit", sigma, count, flush=True)
+    p, pos, mass = _clump(100 + count, 32, count, sigma)
+    mass[::3] *= -0.5                                           # signed contributions cancel exactly
+    ctx = M.pm_create(p, len(pos))
+    rho = dev(np.zeros(64 ** 3))
+    M.pm_deposit(ctx, dev(pos), dev(mass), rho)
+    ref = orc.deposit(oparams(p), pos.astype(np.float64), mass.astype(np.float64))
+    assert rel_max(host(rho).reshape(ref.shape), ref) < 1e-6
+    ctx.close()
+
+
+def test_deposit_wide_ball_is_order_independent(M):
+    p, pos, mass = _clump(7, 32, 1500, 2.0)
+    ctx = M.pm_create(p, len(pos))
+    out = []
+    for seed in (0, 1):
+        o = np.random.default_rng(seed).permutation(len(pos))
+        rho = dev(np.zeros(64 ** 3))
+        M.pm_deposit(ctx, dev(pos[o]), dev(mass[o]), rho)
+        out.append(host(rho))
+    assert np.array_equal(out[0], out[1])
+    ctx.close()
+
+
+def test_deposit_value_that_is_not_finite_reaches_its_cells(M):
+    p, pos, mass = _clump(8, 32, 40, 1.0)
+    mass[3] = np.nan
+    ctx = M.pm_create(p, len(pos))
+    rho = dev(np.zeros(64 ** 3))
+    M.pm_deposit(ctx, dev(pos), dev(mass), rho)
+    got = host(rho)
+    keep = np.delete(np.arange(len(pos)), 3)
+    ref = orc.deposit(oparams(p), pos[keep].astype(np.float64), mass[keep].astype(np.float64)).ravel()
+    assert np.isnan(got).sum() == 251
+    ok = ~np.isnan(got)
+    assert np.max(np.abs(got[ok] - ref[ok])) < 1e-6 * np.max(np.abs(ref))
+    ctx.close()
