@@ -221,7 +221,9 @@ static void derive_sizes(pm_ctx* c, const pm_params* p, int64_t max_particles) {
   c->max_particles = max_particles;
   c->nball = (int)make_ball(p->cutoff * p->sigma).size();
   c->nrows = (int)make_rows(p->cutoff * p->sigma).size();
-  c->npartials = x_blocks(c->N) > z_blocks(c->N) ? x_blocks(c->N) : z_blocks(c->N);
+  c->npartials = 0;
+  for (int b : {x_blocks(c->N, 0), x_blocks(c->N, 1), z_blocks(c->N), zpot_blocks(c->N)})
+    c->npartials = b > c->npartials ? b : c->npartials;
   // A ball of extent up to 8 reaches only the tiles next to its own.
   const int ext = ball_extent(p->cutoff * p->sigma);
   c->plan_ext = (ext >= 1 && ext <= 8) ? ext : 0;
@@ -642,7 +644,7 @@ static pm_status run_solve(pm_ctx* c, const float* rho, const float* H0, float* 
       if (keep_F && c->fspec && k == K) d.spec_in = c->fspec;
       HIPCHK(pass(c, d));
     }
-    if (resid && k >= 2) HIPCHK(reduce_partials(c->partials, x_blocks(N), c->dacc + (k - 1), c->st, run0));
+    if (resid && k >= 2) HIPCHK(reduce_partials(c->partials, x_blocks(N, io), c->dacc + (k - 1), c->st, run0));
     if (dev_tol) HIPCHK(tol_check(c->ctl, c->dacc, k, K, p.tol, N3, c->st));
     k_done = k;
     if (pot) {

@@ -369,17 +369,20 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, const float2* spec_i
 }
 
 // ----------------------------------------------------------------------------
-// x pass for n_pad = 512 and 1024 (rows of H = 256 or 512 complex): a group of
-// LANES lanes per row (16 for H = 256, four rows per wave; 64 for H = 512, one
-// row per wave), four waves per block.  Lane j of a group holds the elements
-// k = j + LANES r (r < RG = H / LANES) of its row for every component, so
-//  - the FFT runs in registers with wave-private LDS exchanges: 16 x 16 for
-//    H = 256, 8 x 8 x 8 for H = 512, and the output is again at
+// x pass for n_pad = 64 to 1024 (rows of H = 32 to 512 complex): a group of
+// LANES = H / 8 lanes per row, so that every lane holds eight elements of it
+// per component.  Lane j of a group holds the elements k = j + LANES r (r < RG =
+// 8) of its row, so
+//  - the FFT runs in registers with wave-private LDS exchanges: 8 x 4, 8 x 8,
+//    8 x 8 x 2, 8 x 8 x 4 and 8 x 8 x 8, and the output is again at
 //    k = j + LANES r;
 //  - the partner H - k of element k (even/odd split of the real transform)
 //    sits in lane LANES - j, register RG - 1 - r (lane 0 pairs within
 //    itself), so the split and merge are cross-lane shuffles;
 //  - nu / mu act on the registers.
+// In the small boxes a block form (rows in LDS, a barrier per stage) took 15, 25
+// and 121 to 150 us for the nu pass at 64^3, 128^3 and 256^3; this form 9.7, 16
+// and 102 us.  Bound: HBM at 256^3 and up, the latency of one wave below.
 // No block-wide barrier is needed after the twiddle table is loaded.
 // ----------------------------------------------------------------------------
 __device__ __forceinline__ void wave_sync() {
@@ -389,26 +392,6 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 __device__ __forceinline__ int xpad(int p) { return p + (p >> 4); }
-
-// 256-point FFT of the group's row held as v[r] = x[j + 16 r]; result in the
-// same layout.  xb: the group's 272-entry LDS row.
-template <bool INV>
-__device__ __forceinline__ void fft256_group(float2* v, float2* xb, int j, const float2* tw_s) {
-  Dft<16, INV>::run(v);                                  // outputs y[16 j + r]
-#pragma unroll
-  for (int r = 0; r < 16; ++r) xb[xpad(16 * j + r)] = v[r];
-  wave_sync();
-#pragma unroll
-  for (int r = 0; r < 16; ++r) v[r] = xb[xpad(j + 16 * r)];
-  wave_sync();
-#pragma unroll
-  for (int r = 1; r < 16; ++r) {
-    float2 w = tw_s[2 * r * j];                          // w_256^(r j) from the 512-entry table
-    if (INV) w.y = -w.y;
-    v[r] = cmul(v[r], w);
-  }
-  Dft<16, INV>::run(v);                                  // outputs y[j + 16 r]
-}
 
 // 512-point FFT of the wave's row held as v[r] = x[j + 64 r], j = lane; result
 // in the same layout.  x = j + 64 r and k = s + 8 a + 64 b: a radix-8 DFT over
@@ -506,37 +489,142 @@ __device__ __forceinline__ void fft256_lane32(float2* v, float2* xb, int j, cons
   for (int r = 0; r < 8; ++r) v[r] = t[r];
 }
 
-#ifndef PM_X256_LANES
-#define PM_X256_LANES 32
-#endif
+// 128-point FFT of a row held by 16 lanes, v[r] = x[j + 16 r], r < 8; result in
+// the same layout.  x = j + 16 r and k = s + 8 q1 + 64 q2: a radix-8 DFT over r
+// (s), twiddles w_128^(j s), for each s the 16 points j = j1 + 2 j2 as a radix-8
+// DFT over j2 (q1), twiddles w_16^(j1 q1) and a radix-2 DFT over j1 (q2).  After
+// the first exchange lane s + 8 j1 holds the values j2; after the second lane
+// s + 8 m holds both j1 of q1 = m + 2 h, which leave X[lane + 16 (h + 4 q2)].
+// tw_s: the 256-entry table w_256^t.
+template <bool INV>
+__device__ __forceinline__ void fft128_lane16(float2* v, float2* xb, int j, const float2* tw_s) {
+  Dft<8, INV>::run(v);
+#pragma unroll
+  for (int s = 1; s < 8; ++s) {
+    float2 w = tw_s[2 * j * s];
+    if (INV) w.y = -w.y;
+    v[s] = cmul(v[s], w);
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) xb[xpad(16 * s + j)] = v[s];
+  wave_sync();
+  const int s = j & 7, hi = j >> 3;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) v[r] = xb[xpad(16 * s + hi + 2 * r)];
+  wave_sync();
+  Dft<8, INV>::run(v);
+#pragma unroll
+  for (int q = 1; q < 8; ++q) {
+    float2 w = tw_s[16 * hi * q];
+    if (INV) w.y = -w.y;
+    v[q] = cmul(v[q], w);
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) xb[xpad(16 * s + 2 * q + hi)] = v[q];
+  wave_sync();
+  float2 t[8];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    const float2 a = xb[xpad(16 * s + 2 * (hi + 2 * h))], b = xb[xpad(16 * s + 2 * (hi + 2 * h) + 1)];
+    t[h] = cadd(a, b);
+    t[h + 4] = csub(a, b);
+  }
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < 8; ++r) v[r] = t[r];
+}
 
+// 64-point FFT of a row held by 8 lanes, v[r] = x[j + 8 r]: radix 8 over r,
+// twiddles w_64^(j s), one exchange, radix 8 over j, which leaves X[s + 8 r] in
+// lane s.  tw_s: w_128^t.
+template <bool INV>
+__device__ __forceinline__ void fft64_lane8(float2* v, float2* xb, int j, const float2* tw_s) {
+  Dft<8, INV>::run(v);
+#pragma unroll
+  for (int s = 1; s < 8; ++s) {
+    float2 w = tw_s[2 * j * s];
+    if (INV) w.y = -w.y;
+    v[s] = cmul(v[s], w);
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) xb[xpad(8 * s + j)] = v[s];
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < 8; ++r) v[r] = xb[xpad(8 * j + r)];
+  wave_sync();
+  Dft<8, INV>::run(v);
+}
+
+// 32-point FFT of a row held by 4 lanes, v[r] = x[j + 4 r]: radix 8 over r,
+// twiddles w_32^(j s), one exchange, after which lane l holds the four j of
+// s = l and s = l + 4; their radix-4 DFTs leave X[l + 4 (h + 2 b)].  tw_s: w_64^t.
+template <bool INV>
+__device__ __forceinline__ void fft32_lane4(float2* v, float2* xb, int j, const float2* tw_s) {
+  Dft<8, INV>::run(v);
+#pragma unroll
+  for (int s = 1; s < 8; ++s) {
+    float2 w = tw_s[2 * j * s];
+    if (INV) w.y = -w.y;
+    v[s] = cmul(v[s], w);
+  }
+#pragma unroll
+  for (int s = 0; s < 8; ++s) xb[xpad(4 * s + j)] = v[s];
+  wave_sync();
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v[4 * h + b] = xb[xpad(4 * (j + 4 * h) + b)];
+  wave_sync();
+  Dft<4, INV>::run(v);
+  Dft<4, INV>::run(v + 4);
+  float2 t[8];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) t[h + 2 * b] = v[4 * h + b];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) v[r] = t[r];
+}
+
+// Rows of H complex by waves: eight elements per lane and component.  Waves per
+// block: four, one or two in the small boxes, whose few rows would otherwise
+// leave CUs without a block (64^3: 256 waves).
 template <int H>
 struct XWave {
   static constexpr int N = 2 * H;
-  static constexpr int LANES = (H == 256) ? PM_X256_LANES : 64;
-  static constexpr int RG = H / LANES;              // elements per lane and component
+  static constexpr int RG = 8;                      // elements per lane and component
+  static constexpr int LANES = H / RG;
   static constexpr int G = 64 / LANES;              // rows per wave
-  static constexpr int ROWS = 4 * G;                // rows per block (4 waves)
+  static constexpr int NW = H == 32 ? 1 : H == 64 ? 2 : 4;
+  static constexpr int NT = 64 * NW;
+  static constexpr int ROWS = NW * G;               // rows per block
   static constexpr int XB = H + H / 16;             // padded LDS row (xpad)
-  static constexpr bool L32 = (H == 256 && LANES == 32);
+  static constexpr bool L32 = H == 256;
   static constexpr int TWL = L32 ? 256 + 32 : 0;    // lane-ordered twiddles of fft256_lane32
   template <bool INV>
   __device__ __forceinline__ static void fft(float2* v, float2* xb, int j, const float2* tw_s,
                                              const float2* twl) {
-    if constexpr (H == 256 && LANES == 16) fft256_group<INV>(v, xb, j, tw_s);
+    if constexpr (H == 32) fft32_lane4<INV>(v, xb, j, tw_s);
+    else if constexpr (H == 64) fft64_lane8<INV>(v, xb, j, tw_s);
+    else if constexpr (H == 128) fft128_lane16<INV>(v, xb, j, tw_s);
     else if constexpr (H == 256) fft256_lane32<INV>(v, xb, j, twl);
     else fft512_wave<INV>(v, xb, j, tw_s);
   }
   // fills the lane-ordered twiddles from the w_N^t table (block-wide)
   __device__ __forceinline__ static void fill_twl(float2* twl, const float2* __restrict__ tw) {
     if constexpr (L32) {
-      for (int t = threadIdx.x; t < TWL; t += 256) {
+      for (int t = threadIdx.x; t < TWL; t += NT) {
         if (t < 256) twl[t] = tw[2 * (t & 31) * (t >> 5)];           // w_256^(j s), j = t % 32, s = t / 32
         else twl[t] = tw[16 * ((t - 256) & 3) * ((t - 256) >> 2)];  // w_32^(j1 q1)
       }
     }
   }
 };
+
+// Which boxes run their x passes by waves: 64^3 to 1024^3, and with FP16
+// spectra 512^3 and up (below, the block form keeps that storage's results the
+// same bits: its tile scales turn any other rounding into a visible change).
+constexpr bool x_by_waves(int N, int io) { return io ? N >= 512 : N >= 64; }
 
 // Occupancy floor (waves per SIMD) asked of the compiler for the fused
 // passes of 256 and 512 points; 1 leaves the register allocation free.  At
@@ -556,7 +644,7 @@ struct XWaves {
 };
 
 template <int H, int XMODE, int NC, int IO = 0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, XMODE>::value))) void k_xpass_wave(float2* spec, const float2* spec_in, long long comp_stride, int ps, float* real,
+__global__ __launch_bounds__(XWave<H>::NT) __attribute__((amdgpu_waves_per_eu(XWaves<H, XMODE>::value))) void k_xpass_wave(float2* spec, const float2* spec_in, long long comp_stride, int ps, float* real,
                                                     long long real_comp_stride, const float2* __restrict__ tw,
                                                     int mu_mode, float inv_a0, float* fprev, double* partials,
                                                     Dipole dip, const float* __restrict__ base, Scales sc,
@@ -572,7 +660,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
   float2* xb = lds + N + (wave * X::G + g) * X::XB;
   float2* twl = lds + N + X::ROWS * X::XB;
   const long long row = (long long)blockIdx.x * X::ROWS + wave * X::G + g;
-  for (int t = threadIdx.x; t < N; t += 256) tw_s[t] = tw[t];
+  for (int t = threadIdx.x; t < N; t += X::NT) tw_s[t] = tw[t];
   X::fill_twl(twl, tw);
   __syncthreads();
 
@@ -672,11 +760,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XWaves<H, X
       }
     }
     if (XK::keep && partials) {
-      __shared__ double red[4];
+      __shared__ double red[X::NW];
       for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
       if (lane == 0) red[wave] = acc;
       __syncthreads();
-      if (threadIdx.x == 0) partials[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+      if (threadIdx.x == 0) {
+        double t = red[0];
+        for (int w = 1; w < X::NW; ++w) t += red[w];
+        partials[blockIdx.x] = t;
+      }
     }
   }
 
@@ -1804,10 +1896,10 @@ hipError_t launch_x(const FftGeom& g, float2* spec, float* real, long long real_
                     const float* base = nullptr, Coarse co = Coarse{}, const float2* spec_in = nullptr) {
   if (!spec_in) spec_in = spec;
   using C = Cfg<N>;
-  if constexpr (N == 512 || N == 1024) {
+  if constexpr (x_by_waves(N, IO)) {
     using X = XWave<N / 2>;
     const size_t sh = sizeof(float2) * (N + (size_t)X::ROWS * X::XB + X::TWL);
-    hipLaunchKernelGGL((k_xpass_wave<N / 2, XMODE, NC, IO>), dim3(N * N / X::ROWS), dim3(256), sh, st, spec, spec_in,
+    hipLaunchKernelGGL((k_xpass_wave<N / 2, XMODE, NC, IO>), dim3(N * N / X::ROWS), dim3(X::NT), sh, st, spec, spec_in,
                        g.comp_stride, g.ps, real, real_cs, g.tw, mu_mode, inv_a0, fprev, partials, dip, base, g.sc,
                        g.gate, co);
     return hipGetLastError();
@@ -1987,9 +2079,16 @@ __global__ __launch_bounds__(1024) void k_reduce_partials(const double* __restri
   }
 }
 
-int x_blocks(int N) {
-  if (N == 512) return N * N / XWave<256>::ROWS;
-  if (N == 1024) return N * N / XWave<512>::ROWS;
+int x_blocks(int N, int io) {
+  if (x_by_waves(N, io)) {
+    switch (N) {
+      case 64: return N * N / XWave<32>::ROWS;
+      case 128: return N * N / XWave<64>::ROWS;
+      case 256: return N * N / XWave<128>::ROWS;
+      case 512: return N * N / XWave<256>::ROWS;
+      case 1024: return N * N / XWave<512>::ROWS;
+    }
+  }
   const int H = N / 2;
   int rows = 1024 / H;
   rows = rows < 1 ? 1 : (rows > 64 ? 64 : rows);

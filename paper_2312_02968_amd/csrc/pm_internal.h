@@ -159,7 +159,7 @@ hipError_t reduce_partials(const double* partials, int n, double* out, hipStream
 // gate_advance: ctl[0] 1 -> 2.
 hipError_t tol_check(int* ctl, const double* acc, int k, int kmax, double tol, double n3, hipStream_t st);
 hipError_t gate_advance(int* ctl, hipStream_t st);
-int x_blocks(int N);
+int x_blocks(int N, int io);      // x-pass blocks (partials of the residual); io as PassDesc::io
 int z_blocks(int N);
 int zpot_blocks(int N);           // z-pass blocks of the potential form
 int z_blocks_io(int N, int io);   // z-pass blocks with half-precision spectra (io != 0)
