@@ -1273,16 +1273,8 @@ pm_status pm_net_create(int32_t n, int32_t max_batch, void* stream, pm_net** out
   NALLOC(b.target, 3 * V1);
   NALLOC(b.rms, (size_t)max_batch);
   NALLOC(b.sums, (size_t)max_batch + 64);
-  // weight-gradient partial sums (the launch picks its number of brick groups
-  // to fit; the largest layer, b3b at 64 x 64, still gets 606)
-  b.partial_floats = net::kWgradPartialFloats;
+  b.partial_floats = net::kWgradPartialFloats;   // weight-gradient partial sums
   NALLOC(b.partial, (size_t)b.partial_floats);
-  size_t wmax = 0;   // largest weight tensor (b3b: 27 x 64 x 64)
-  for (int l = 0; l < net::NLAYER; ++l) {
-    const size_t cnt = (size_t)net::kLayers[l].taps * net::kLayers[l].cin * net::kLayers[l].cout;
-    wmax = cnt > wmax ? cnt : wmax;
-  }
-  NALLOC(b.partial2, (size_t)net::kWgradSlices * wmax);
   b.dpartial_count = 1024 * 52;
   NALLOC(b.dpartial, (size_t)b.dpartial_count);
 #undef NALLOC

@@ -60,11 +60,9 @@ constexpr int NT = 256;
 constexpr int BX = 16, BY = PM_CONV_BY, BZ = 4;
 constexpr int HX = BX + 2, HY = BY + 2, HZ = BZ + 2;
 constexpr int HSLOTS = HX * HY * HZ;
-// weight-gradient brick: 16 x 4 x 2 voxels
-constexpr int WBX = 16, WBY = 4, WBZ = 2;
-constexpr int WROWS = (WBY + 2) * (WBZ + 2);
-constexpr int WXS = 3 * WROWS * WBX + 8;   // LDS stride of one input channel (3 x-shifted copies)
-constexpr int WGROUPS = kWgradGroups;
+// weight-gradient brick: 16 x 4 x 4 voxels, one wave for each dz of the taps
+constexpr int WBY = 4, WVOX = BX * WBY * BZ, WT = 192;
+static_assert(WBY == BY, "the weight gradient stages the halo brick of the convolutions");
 constexpr int RGROUPS = 1024;              // blocks of the reductions over voxels
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
@@ -203,172 +201,182 @@ struct WgradArgs {
   const bf16* src0;
   const bf16* src1;
   const bf16* gz;     // [batch][n^3][COUT]
-  float* partial;     // [G][27][CIN][COUT]
-  int n, batch, G;
+  float* partial;     // [G][27 CIN COUT weight sums, then COUT bias sums]
+  int n, batch, per;  // per: bricks of one block
 };
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+
+// 8 bf16 of one channel from two rows of 16 voxels x 16 channels in LDS
+// (channels last, 512 bytes a row): lane (m, g) gets channel m of voxels
+// 4 g .. 4 g + 3 of the row at r0, then of the row at r1.  A transposing read
+// moves 16 lanes' 8-byte pieces, so a row is read end to end by the 64 lanes
+// (pass r0 and r1 with the lane's own 8 bytes already added).
+__device__ __forceinline__ bf16x8 tr_rows(const bf16* r0, const bf16* r1) {
+  struct Two { s16x4 a, b; } v{__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)r0),
+                               __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)r1)};
+  return __builtin_bit_cast(bf16x8, v);
+}
 
 // Weight gradient gw[t][c][o] = sum_v in[v + tap_t][c] gz[v][o] as a GEMM
 // with the voxels as the reduction axis: A = gz^T (16 output channels x 32
-// voxels), B = the shifted input (32 voxels x 16 input channels of one tap).
-// Block (G, CIN / 16): brick group blockIdx.x, channel chunk blockIdx.y.  Both
-// operands are staged transposed in LDS (voxels contiguous), the input in
-// three copies shifted by dx = -1, 0, 1 so that every 8-voxel read is aligned.
-// Wave w owns output tile mt = w mod (COUT / 16) and the taps t = q, q + WPM,
-// ... with q = w / (COUT / 16).
+// voxels), B = the shifted input (32 voxels x 16 input channels of one tap),
+// and the bias gradient sum_v gz[v][o] as the same product with ones.  Block
+// (group, CIN / 16): bricks of group blockIdx.x, channel chunk blockIdx.y.
+// Wave w owns the 9 taps with dz = w - 1 and every output tile.  Both bricks
+// stand in LDS as in memory, channels last, and are turned by the transposing
+// reads; 32 voxels are two x rows, neighbours in z, so that one fragment of
+// the input serves the three taps dy (of three different rows of gz).
+// Bound: LDS reads and the latency of a brick's loads, about even with the
+// matrix pipe at 16 output channels.  16 to 16 channels on four 64^3 grids
+// take 36 us and their reduction 7; both bricks staged transposed by 2-byte
+// LDS writes, with three shifted copies of the input, and one group per 4
+// bricks took 70 and 29 us (96 to 32 channels on 32^3: 50 and 11 us, before
+// 115 and 103 with 268 MB of partial sums), and the bias gradient, a kernel of
+// its own, another 74.
 template <int CIN, int COUT, int C0>
-__global__ __launch_bounds__(NT) void k_wgrad(WgradArgs a) {
+__global__ __launch_bounds__(WT) void k_wgrad(WgradArgs a) {
   constexpr int MT = COUT / 16;
-  constexpr int WPM = 4 / MT;
-  constexpr int NTAP = (27 + WPM - 1) / WPM;
-  constexpr int GS = WBX * WBY * WBZ + 8;
-  __shared__ bf16 xin[16 * WXS];
-  __shared__ bf16 gzT[COUT * GS];
+  constexpr int XU = HSLOTS * 2, GU = WVOX * (COUT / 8);   // 16-byte units of the two bricks
+  constexpr int XN = (XU + WT - 1) / WT, GN = (GU + WT - 1) / WT;
+  __shared__ uint4 xin4[XU];
+  __shared__ uint4 gz4[GU];   // [COUT / 16][voxel][16]
+  const bf16* xin = reinterpret_cast<const bf16*>(xin4);
+  const bf16* gzl = reinterpret_cast<const bf16*>(gz4);
 
   const int ch = blockIdx.y;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, m = lane & 15, g = lane >> 4;
-  const int mt = wave % MT, q = wave / MT;
   const int n = a.n;
-  const int nbx = (n + WBX - 1) / WBX, nby = (n + WBY - 1) / WBY, nbz = (n + WBZ - 1) / WBZ;
+  const int nbx = (n + BX - 1) / BX, nby = (n + WBY - 1) / WBY, nbz = (n + BZ - 1) / BZ;
   const int nbricks = nbx * nby * nbz * a.batch;
+  const bool bias = ch == 0 && wave == 0;
+  const bf16x8 ones = as_bf16x8(make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
 
-  f32x4 acc[NTAP];
+  f32x4 acc[3][3][MT], accb[MT];   // [dy][dx]
 #pragma unroll
-  for (int i = 0; i < NTAP; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < MT; ++t) {
+    accb[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc[k / 3][k % 3][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
-  for (int br = blockIdx.x; br < nbricks; br += a.G) {
+  const int br0 = blockIdx.x * a.per, br1 = min(br0 + a.per, nbricks);
+  for (int br = br0; br < br1; ++br) {
     int r_ = br;
-    const int bx = r_ % nbx;
+    const int x0 = (r_ % nbx) * BX;
     r_ /= nbx;
-    const int by = r_ % nby;
+    const int y0 = (r_ % nby) * WBY;
     r_ /= nby;
-    const int bz = r_ % nbz;
+    const int z0 = (r_ % nbz) * BZ;
     const int b = r_ / nbz;
-    const int x0 = bx * WBX, y0 = by * WBY, z0 = bz * WBZ;
-    __syncthreads();
-    for (int u = tid; u < WBX * WBY * WBZ * (COUT / 8); u += NT) {
+    uint4 xv[XN], gv[GN];
+#pragma unroll
+    for (int k = 0; k < XN; ++k) {
+      const int u = tid + k * WT;
+      const int half = u & 1, slot = u >> 1;
+      const int sx = slot % HX, sy = (slot / HX) % (WBY + 2), sz = slot / (HX * (WBY + 2));
+      if (u < XU)
+        xv[k] = load_in8<CIN, C0>(a.src0, a.src1, n, b, x0 - 1 + sx, y0 - 1 + sy, z0 - 1 + sz, ch * 16 + half * 8);
+    }
+#pragma unroll
+    for (int k = 0; k < GN; ++k) {
+      const int u = tid + k * WT;
       const int v = u / (COUT / 8), og = u % (COUT / 8);
-      const int x = v % WBX, y = (v / WBX) % WBY, z = v / (WBX * WBY);
-      const int gx = x0 + x, gy = y0 + y, gzz = z0 + z;
-      uint4 val = make_uint4(0u, 0u, 0u, 0u);
-      if (gx < n && gy < n && gzz < n) {
+      const int gx = x0 + v % BX, gy = y0 + (v / BX) % WBY, gzz = z0 + v / (BX * WBY);
+      gv[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (u < GU && gx < n && gy < n && gzz < n) {
         const int64_t idx = (((int64_t)b * n + gzz) * n + gy) * n + gx;
-        val = *reinterpret_cast<const uint4*>(a.gz + idx * COUT + og * 8);
-      }
-      const bf16* e = reinterpret_cast<const bf16*>(&val);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) gzT[(og * 8 + i) * GS + v] = e[i];
-    }
-    for (int u = tid; u < WROWS * (WBX + 2) * 2; u += NT) {
-      const int half = u & 1, rest = u >> 1;
-      const int hx = rest % (WBX + 2), row = rest / (WBX + 2);
-      const int sy = row % (WBY + 2), sz = row / (WBY + 2);
-      const uint4 val = load_in8<CIN, C0>(a.src0, a.src1, n, b, x0 - 1 + hx, y0 - 1 + sy, z0 - 1 + sz,
-                                          ch * 16 + half * 8);
-      const bf16* e = reinterpret_cast<const bf16*>(&val);
-#pragma unroll
-      for (int dxs = 0; dxs < 3; ++dxs) {
-        const int xx = hx - dxs;
-        if (xx >= 0 && xx < WBX) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) xin[(half * 8 + i) * WXS + (row * 3 + dxs) * WBX + xx] = e[i];
-        }
+        gv[k] = *reinterpret_cast<const uint4*>(a.gz + idx * COUT + og * 8);
       }
     }
     __syncthreads();
 #pragma unroll
-    for (int ks = 0; ks < (WBX * WBY * WBZ) / 32; ++ks) {
-      const int r = 2 * ks + (g >> 1), xg = 8 * (g & 1);
-      const int y = r % WBY, z = r / WBY;
-      const bf16x8 af = *reinterpret_cast<const bf16x8*>(gzT + (16 * mt + m) * GS + 32 * ks + 8 * g);
+    for (int k = 0; k < XN; ++k) {
+      const int u = tid + k * WT;
+      if (u < XU) xin4[u] = xv[k];
+    }
 #pragma unroll
-      for (int i = 0; i < NTAP; ++i) {
-        const int t = q + i * WPM;
-        if (t < 27) {
-          const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-          const int row = (z + 1 + dz) * (WBY + 2) + (y + 1 + dy);
-          const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(xin + m * WXS + (row * 3 + dx + 1) * WBX + xg);
-          acc[i] = mfma(af, bfr, acc[i]);
+    for (int k = 0; k < GN; ++k) {
+      const int u = tid + k * WT;
+      const int v = u / (COUT / 8), og = u % (COUT / 8);
+      if (u < GU) gz4[((og >> 1) * WVOX + v) * 2 + (og & 1)] = gv[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int zp = 0; zp < BZ; zp += 2) {
+      bf16x8 af[WBY][MT];
+#pragma unroll
+      for (int y = 0; y < WBY; ++y)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          const bf16* r = gzl + (t * WVOX + (zp * WBY + y) * BX) * 16 + lane * 4;
+          af[y][t] = tr_rows(r, r + WBY * BX * 16);
         }
+      if (bias) {
+#pragma unroll
+        for (int y = 0; y < WBY; ++y)
+#pragma unroll
+          for (int t = 0; t < MT; ++t) accb[t] = mfma(af[y][t], ones, accb[t]);
       }
+#pragma unroll
+      for (int yy = 0; yy < WBY + 2; ++yy)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+          const bf16* r = xin + (((zp + wave) * (WBY + 2) + yy) * HX + dx) * 16 + lane * 4;
+          const bf16x8 bfr = tr_rows(r, r + (WBY + 2) * HX * 16);
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy) {
+            const int y = yy - dy;
+            if (y >= 0 && y < WBY) {
+#pragma unroll
+              for (int t = 0; t < MT; ++t) acc[dy][dx][t] = mfma(af[y][t], bfr, acc[dy][dx][t]);
+            }
+          }
+        }
     }
   }
-  // lane holds D[o = 16 mt + 4 g + j][c = m]
-  float* P = a.partial + (int64_t)blockIdx.x * 27 * CIN * COUT;
+  // lane holds D[o = 16 t + 4 g + j][c = m]
+  float* P = a.partial + (int64_t)blockIdx.x * wgrad_stride(CIN, COUT);
 #pragma unroll
-  for (int i = 0; i < NTAP; ++i) {
-    const int t = q + i * WPM;
-    if (t < 27) {
+  for (int k = 0; k < 9; ++k)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) P[((int64_t)t * CIN + ch * 16 + m) * COUT + 16 * mt + 4 * g + j] = acc[i][j];
-    }
+    for (int t = 0; t < MT; ++t)
+      *reinterpret_cast<f32x4*>(P + ((int64_t)(9 * wave + k) * CIN + ch * 16 + m) * COUT + 16 * t + 4 * g) =
+          acc[k / 3][k % 3][t];
+  if (bias && m == 0) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+      *reinterpret_cast<f32x4*>(P + 27 * CIN * COUT + 16 * t + 4 * g) = accb[t];
   }
 }
 
-// Two-stage sum over the brick groups.  Stage 1: part2[s][i] = sum over the
-// groups of slice s (blockIdx.y) of partial[g][t][c][o], with
-// i = (t cin_real + c) COUT + o and c < cin_real.
-__global__ __launch_bounds__(NT) void k_reduce_wgrad1(const float* __restrict__ partial, int G, int S, int CIN,
-                                                      int COUT, int cin_real, float* __restrict__ part2) {
-  const int64_t count = 27LL * cin_real * COUT;
-  const int64_t stride = 27LL * CIN * COUT;
-  const int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x;
-  if (i >= count) return;
-  const int o = (int)(i % COUT);
-  const int64_t tc = i / COUT;
-  const int c = (int)(tc % cin_real), t = (int)(tc / cin_real);
-  const int64_t src = ((int64_t)t * CIN + c) * COUT + o;
-  const int s = blockIdx.y;
-  const int g0 = (int)((int64_t)G * s / S), g1 = (int)((int64_t)G * (s + 1) / S);
+// out[i] = sum over the G groups of the layer's weight sums (input channels
+// below cin_real), then its bias sums; the flat gradient holds them in this
+// order.  A block takes 64 consecutive sums, its 16 waves every 16th group.
+__global__ __launch_bounds__(1024) void k_reduce_wgrad(const float* __restrict__ partial, int G, int CIN, int COUT,
+                                                       int cin_real, float* __restrict__ out) {
+  __shared__ float red[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int count = 27 * cin_real * COUT, stride = wgrad_stride(CIN, COUT);
+  const int i = blockIdx.x * 64 + lane;
+  int src = 0;
+  if (i < count) {
+    const int tc = i / COUT;
+    src = (tc / cin_real * CIN + tc % cin_real) * COUT + i % COUT;
+  } else if (i < count + COUT) {
+    src = 27 * CIN * COUT + i - count;
+  }
   float acc = 0.0f;
-  for (int gi = g0; gi < g1; ++gi) acc += partial[gi * stride + src];
-  part2[s * count + i] = acc;
-}
-
-// Stage 2: out[i] = sum over slices of part2[s][i].
-__global__ __launch_bounds__(NT) void k_reduce_wgrad2(const float* __restrict__ part2, int S, int64_t count,
-                                                      float* __restrict__ out) {
-  const int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x;
-  if (i >= count) return;
-  float acc = 0.0f;
-  for (int s = 0; s < S; ++s) acc += part2[s * count + i];
-  out[i] = acc;
-}
-
-// partial[block][c] = sum over this block's voxels of g[v][c]; a thread reads
-// 8 channels (16 bytes) at a time (C a multiple of 8 dividing 256)
-__global__ __launch_bounds__(NT) void k_colsum(const bf16* __restrict__ g, int64_t nvox, int C, float* partial) {
-  __shared__ float red[NT * 8];
-  const int groups = C / 8, cg = threadIdx.x % groups, lanes = NT / groups, l = threadIdx.x / groups;
-  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int64_t v = blockIdx.x * (int64_t)lanes + l; v < nvox; v += (int64_t)gridDim.x * lanes) {
-    const uint4 u = *reinterpret_cast<const uint4*>(g + v * C + cg * 8);
-    const bf16* e = reinterpret_cast<const bf16*>(&u);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] += bf(e[i]);
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) red[threadIdx.x * 8 + i] = s[i];
+#pragma unroll 8
+  for (int gi = wave; gi < G; gi += 16) acc += partial[(int64_t)gi * stride + src];
+  red[wave][lane] = acc;
   __syncthreads();
-  if (threadIdx.x < C) {
-    const int c = threadIdx.x, g8 = c / 8, i = c % 8;
+  if (wave == 0 && i < count + COUT) {
     float t = 0.0f;
-    for (int k = 0; k < lanes; ++k) t += red[(k * groups + g8) * 8 + i];
-    partial[blockIdx.x * C + c] = t;
-  }
-}
-
-// out[c] = sum over k of partial[k * C + c]; one block, C divides 256
-__global__ __launch_bounds__(NT) void k_reduce_cols(const float* __restrict__ partial, int nblk, int C, float* out) {
-  __shared__ float red[NT];
-  const int c = threadIdx.x % C, lanes = NT / C;
-  float s = 0.0f;
-  for (int k = threadIdx.x / C; k < nblk; k += lanes) s += partial[k * C + c];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < C) {
-    float t = 0.0f;
-    for (int l = 0; l < lanes; ++l) t += red[l * C + threadIdx.x];
-    out[threadIdx.x] = t;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += red[w][lane];
+    out[i] = t;
   }
 }
 
@@ -474,15 +482,35 @@ __global__ __launch_bounds__(NT) void k_poolgrad(const bf16* __restrict__ gcat, 
 }
 
 // Block reduction of NV doubles per thread into part[blockIdx.x * NV + k].
+// Many values are halved with their lanes (63 exchanges for up to 64 values
+// instead of 6 each: lane k ends with the sum of value k).
 template <int NV>
 __device__ void block_reduce_store(double (&v)[NV], double* part) {
-  __shared__ double red[NT / 64][NV];
+  constexpr int NR = NV > 8 ? 64 : NV;
+  static_assert(NV <= 64, "one lane per value");
+  __shared__ double red[NT / 64][NR];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if constexpr (NV > 8) {
+    double w[64];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    double s = v[k];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) red[wave][k] = s;
+    for (int k = 0; k < 64; ++k) w[k] = k < NV ? v[k < NV ? k : 0] : 0.0;
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) {
+      const bool up = lane & h;
+#pragma unroll
+      for (int k = 0; k < h; ++k) {
+        const double keep = up ? w[k + h] : w[k], send = up ? w[k] : w[k + h];
+        w[k] = keep + __shfl_xor(send, h, 64);
+      }
+    }
+    red[wave][lane] = w[0];
+  } else {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      double s = v[k];
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+      if (lane == 0) red[wave][k] = s;
+    }
   }
   __syncthreads();
   for (int k = threadIdx.x; k < NV; k += NT) {
@@ -492,23 +520,19 @@ __device__ void block_reduce_store(double (&v)[NV], double* part) {
   }
 }
 
-// out[k] = sum over blocks of part[b * nv + k] (FP64); one block, all threads
-// share every k
+// out[k] = sum over blocks of part[b * nv + k] (FP64); block k of nv
 __global__ __launch_bounds__(NT) void k_reduce_d(const double* __restrict__ part, int nblk, int nv, double* out) {
   __shared__ double red[NT / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int k = 0; k < nv; ++k) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += NT) s += part[b * nv + k];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) red[wave] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int w = 0; w < NT / 64; ++w) t += red[w];
-      out[k] = t;
-    }
-    __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = blockIdx.x;
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += NT) s += part[b * nv + k];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < NT / 64; ++w) t += red[w];
+    out[k] = t;
   }
 }
 
@@ -814,35 +838,23 @@ hipError_t conv(const bf16* s0, const bf16* s1, const bf16* w, const float* bias
 template <int CIN, int COUT, int C0>
 hipError_t wgrad(const Buffers& B, int layer, const bf16* s0, const bf16* s1, const bf16* gz, int n, int batch,
                  hipStream_t st) {
-  // as many brick groups as the partial-sum buffer holds (up to 2048), so that
-  // even the 16-channel layers put several blocks on every CU
-  const int nbricks = ((n + WBX - 1) / WBX) * ((n + WBY - 1) / WBY) * ((n + WBZ - 1) / WBZ) * batch;
-  int64_t gmax = B.partial_floats / (27LL * CIN * COUT);
-  if (gmax > WGROUPS) gmax = WGROUPS;
-  const int G = nbricks < gmax ? nbricks : (int)gmax;
-  if (G < 1 || (int64_t)G * 27 * CIN * COUT > B.partial_floats) {
+  // The partial sums of a group are written once and read once, so groups are
+  // few: kWgradBlocks blocks in all, and every block the same number of bricks
+  // but the last.
+  const int nbricks = conv_blocks(n, batch);
+  const int groups = kWgradBlocks / (CIN / 16);
+  const int per = (nbricks + groups - 1) / groups, G = (nbricks + per - 1) / per;
+  if (G < 1 || (int64_t)G * wgrad_stride(CIN, COUT) > B.partial_floats) {
     g_where = "weight-gradient partial buffer too small";
     return hipErrorInvalidValue;
   }
-  WgradArgs a{s0, s1, gz, B.partial, n, batch, G};
-  hipLaunchKernelGGL((k_wgrad<CIN, COUT, C0>), dim3(G, CIN / 16), dim3(NT), 0, st, a);
+  WgradArgs a{s0, s1, gz, B.partial, n, batch, per};
+  hipLaunchKernelGGL((k_wgrad<CIN, COUT, C0>), dim3(G, CIN / 16), dim3(WT), 0, st, a);
   NETCHK(launched("k_wgrad"));
-  const int cin_real = kLayers[layer].cin;
-  const int64_t cnt = 27LL * cin_real * COUT;
-  const int S = G < kWgradSlices ? G : kWgradSlices;
-  const int nbx = (int)((cnt + NT - 1) / NT);
-  hipLaunchKernelGGL(k_reduce_wgrad1, dim3(nbx, S), dim3(NT), 0, st, B.partial, G, S, CIN, COUT, cin_real,
-                     B.partial2);
-  NETCHK(launched("k_reduce_wgrad1"));
-  hipLaunchKernelGGL(k_reduce_wgrad2, dim3(nbx), dim3(NT), 0, st, B.partial2, S, cnt,
+  const int cin_real = kLayers[layer].cin, cnt = 27 * cin_real * COUT + COUT;
+  hipLaunchKernelGGL(k_reduce_wgrad, dim3((cnt + 63) / 64), dim3(1024), 0, st, B.partial, G, CIN, COUT, cin_real,
                      B.grads + weight_offset(layer));
-  NETCHK(launched("k_reduce_wgrad2"));
-  const int64_t nvox = level_voxels(n, 0) * batch;
-  const int nb = grid_for(nvox / (NT / (COUT / 8)) + 1);
-  hipLaunchKernelGGL(k_colsum, dim3(nb), dim3(NT), 0, st, gz, nvox, COUT, B.partial);
-  NETCHK(launched("k_colsum"));
-  hipLaunchKernelGGL(k_reduce_cols, dim3(1), dim3(NT), 0, st, B.partial, nb, COUT, B.grads + bias_offset(layer));
-  return launched("k_reduce_cols");
+  return launched("k_reduce_wgrad");
 }
 
 template <int C>
@@ -906,7 +918,7 @@ hipError_t loss_backward(const Buffers& B, int batch, hipStream_t st) {
                      B.target, B.g16a, nvox, batch, inv_count, B.dpartial);
   NETCHK(launched("k_head"));
   double* hs = B.sums + B.max_batch + 1;   // 52 head sums
-  hipLaunchKernelGGL(k_reduce_d, dim3(1), dim3(NT), 0, st, B.dpartial, nb, 52, hs);
+  hipLaunchKernelGGL(k_reduce_d, dim3(52), dim3(NT), 0, st, B.dpartial, nb, 52, hs);
   NETCHK(launched("k_reduce_d"));
   hipLaunchKernelGGL(k_head_grads, dim3(1), dim3(64), 0, st, hs, B.grads + weight_offset(OUT),
                      B.grads + bias_offset(OUT), B.sums + B.max_batch, inv_count);
