@@ -47,17 +47,12 @@ hipError_t launched(const char* what) {
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NT = 256;
-#ifndef PM_CONV_PAD
-#define PM_CONV_PAD 0
-#endif
-#ifndef PM_CONV_BY
-#define PM_CONV_BY 4
-#endif
 // forward / backward-data brick: 16 x 4 x 4 voxels, one z plane per wave
-constexpr int BX = 16, BY = PM_CONV_BY, BZ = 4;
+constexpr int BX = 16, BY = 4, BZ = 4;
 constexpr int HX = BX + 2, HY = BY + 2, HZ = BZ + 2;
 constexpr int HSLOTS = HX * HY * HZ;
 // weight-gradient brick: 16 x 4 x 4 voxels, one wave for each dz of the taps
@@ -106,18 +101,24 @@ struct ConvArgs {
 };
 
 // out[v][o] = bias[o] + sum over taps t and channels c of in[v + tap_t][c] w[o][t][c],
-// then ReLU and the mask.  A block owns a 16 x 4 x 4 brick; wave w computes
-// its z plane w as 4 rows (M tiles of 16 voxels along x) times COUT / 16
-// N tiles.  The input halo brick is staged in LDS in chunks of CC channels;
-// a k step of 32 covers 32 / CC taps of one chunk.
-template <int CIN, int COUT, int C0, bool RELU>
+// then ReLU and the mask.  A block owns a 16 x 4 x 4 brick and NTB of the
+// COUT / 16 output tiles; wave w computes its z plane w as 4 rows of 16
+// voxels along x.  The input halo brick is staged in LDS in chunks of CC
+// channels, the next chunk's loads under way while one is multiplied; a k
+// step of 32 covers 32 / CC taps of one chunk.  The weights are the rows of
+// the product, so that a lane ends with 4 neighbouring channels of one voxel
+// (8-byte stores, whole lines to a wave).  Bound: LDS reads (12 us of the 31
+// that 16 to 16 channels take on four 64^3 grids) and the latency of a brick's
+// loads.  Loads one unit at a time, tap offsets computed per lane and 2-byte
+// stores took 41 us there, 131 from 48 to 16 channels (now 75), 111 from 16 to
+// 48 (82).
+template <int CIN, int COUT, int C0, int NTB, bool RELU>
 __global__ __launch_bounds__(NT) void k_conv(ConvArgs a) {
   constexpr int CC = (CIN % 32 == 0) ? 32 : 16;
-  constexpr int CS = CC + PM_CONV_PAD;   // voxel slot stride in LDS (bf16); padding measured no faster
   constexpr int NCH = CIN / CC;
   constexpr int KS = (27 * CC + 31) / 32;
-  constexpr int NTL = COUT / 16;
-  __shared__ uint4 tile4[HSLOTS * CS / 8];
+  constexpr int UNITS = HSLOTS * (CC / 8), UN = (UNITS + NT - 1) / NT;   // 16-byte units of a chunk
+  __shared__ uint4 tile4[UNITS];
 
   const int n = a.n;
   const int nbx = (n + BX - 1) / BX, nby = (n + BY - 1) / BY, nbz = (n + BZ - 1) / BZ;
@@ -128,70 +129,93 @@ __global__ __launch_bounds__(NT) void k_conv(ConvArgs a) {
   bid /= nby;
   const int bz = bid % nbz;
   const int b = bid / nbz;
-  const int x0 = bx * BX, y0 = by * BY, z0 = bz * BZ;
+  const int x0 = bx * BX, y0 = by * BY, z0 = bz * BZ, o0 = blockIdx.y * (NTB * 16);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, m = lane & 15, g = lane >> 4;
 
-  f32x4 acc[BY][NTL];
+  f32x4 acc[BY][NTB];
 #pragma unroll
   for (int i = 0; i < BY; ++i)
 #pragma unroll
-    for (int t = 0; t < NTL; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NTB; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  uint4 pre[UN];
+  auto load = [&](int ch) {
+#pragma unroll
+    for (int k = 0; k < UN; ++k) {
+      const int u = tid + k * NT, slot = u / (CC / 8), cg = u % (CC / 8);
+      const int sx = slot % HX, sy = (slot / HX) % HY, sz = slot / (HX * HY);
+      if (u < UNITS)
+        pre[k] = load_in8<CIN, C0>(a.src0, a.src1, n, b, x0 - 1 + sx, y0 - 1 + sy, z0 - 1 + sz, ch * CC + cg * 8);
+    }
+  };
+  load(0);
+
+  // lane (m, g) holds k = 8 g .. 8 g + 7 of a step: with 16 channels the upper
+  // lanes (hi) take the step's second tap, one voxel on, or one row or one
+  // plane on where dx = 1 is the first's
+  const int hi = CC == 16 ? g >> 1 : 0, c8 = CC == 16 ? g & 1 : g;
+  const uint4* const tl = tile4 + (wave * HY * HX + m) * (CC / 8) + c8;
+  const uint4* const tx = tl + hi * (CC / 8);
+  const uint4* const ty = tl + hi * (HX - 2) * (CC / 8);
+  const uint4* const tz = tl + hi * ((HY - 2) * HX - 2) * (CC / 8);
+  const bf16* const wl = a.w + ((int64_t)(o0 + m) * 27 + hi) * CIN + c8 * 8;
+
+#pragma unroll 1
   for (int ch = 0; ch < NCH; ++ch) {
     if (ch) __syncthreads();
-    for (int u = tid; u < HSLOTS * (CC / 8); u += NT) {
-      const int slot = u / (CC / 8), cg = u % (CC / 8);
-      const int sx = slot % HX, sy = (slot / HX) % HY, sz = slot / (HX * HY);
-      tile4[(slot * CS + cg * 8) / 8] =
-          load_in8<CIN, C0>(a.src0, a.src1, n, b, x0 - 1 + sx, y0 - 1 + sy, z0 - 1 + sz, ch * CC + cg * 8);
+#pragma unroll
+    for (int k = 0; k < UN; ++k) {
+      const int u = tid + k * NT;
+      if (u < UNITS) tile4[u] = pre[k];
     }
     __syncthreads();
+    if (ch + 1 < NCH) load(ch + 1);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int k0 = ks * 32 + 8 * g;
-      const int tap = k0 / CC, c = k0 % CC;
-      const bool valid = tap < 27;
-      const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-      bf16x8 bw[NTL];
+      const int tap = CC == 16 ? 2 * ks : ks;   // of the lanes below hi
+      const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
+      const bool valid = tap + hi < 27;
+      const uint4* const p = CC == 32 ? tl : dx < 2 ? tx : dy < 2 ? ty : tz;
+      bf16x8 bw[NTB];
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) {
+      for (int t = 0; t < NTB; ++t) {
         uint4 wv = make_uint4(0u, 0u, 0u, 0u);
-        if (valid) wv = *reinterpret_cast<const uint4*>(a.w + ((int64_t)(16 * t + m) * 27 + tap) * CIN + ch * CC + c);
+        if (valid) wv = *reinterpret_cast<const uint4*>(wl + (int64_t)(16 * t * 27 + tap) * CIN + ch * CC);
         bw[t] = as_bf16x8(wv);
       }
 #pragma unroll
       for (int i = 0; i < BY; ++i) {
         uint4 av = make_uint4(0u, 0u, 0u, 0u);
-        if (valid) {
-          const int slot = ((wave + 1 + dz) * HY + (i + 1 + dy)) * HX + (m + 1 + dx);
-          av = tile4[(slot * CS + c) / 8];
-        }
+        if (valid) av = p[((dz * HY + i + dy) * HX + dx) * (CC / 8)];
         const bf16x8 af = as_bf16x8(av);
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) acc[i][t] = mfma(af, bw[t], acc[i][t]);
+        for (int t = 0; t < NTB; ++t) acc[i][t] = mfma(bw[t], af, acc[i][t]);
       }
     }
   }
 
-  // lane holds voxel x = 4 g + j of row i, channel o = 16 t + m
-  const int gz = z0 + wave;
+  // lane holds channels 16 t + 4 g + j of voxel x = m of row i
+  const int gx = x0 + m, gz = z0 + wave;
 #pragma unroll
-  for (int i = 0; i < BY; ++i) {
-    const int gy = y0 + i;
+  for (int t = 0; t < NTB; ++t) {
+    const int o = o0 + 16 * t + 4 * g;
+    f32x4 bo = {0.f, 0.f, 0.f, 0.f};
+    if (a.bias) bo = f32x4{a.bias[o], a.bias[o + 1], a.bias[o + 2], a.bias[o + 3]};
 #pragma unroll
-    for (int t = 0; t < NTL; ++t) {
-      const int o = 16 * t + m;
-      const float bo = a.bias ? a.bias[o] : 0.0f;
+    for (int i = 0; i < BY; ++i) {
+      const int gy = y0 + i;
+      if (gx < n && gy < n && gz < n) {
+        const int64_t idx = ((((int64_t)b * n + gz) * n + gy) * n + gx) * COUT + o;
+        bf16x4 mk, r;
+        if (a.mask) mk = *reinterpret_cast<const bf16x4*>(a.mask + idx);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int gx = x0 + 4 * g + j;
-        if (gx < n && gy < n && gz < n) {
-          const int64_t idx = (((int64_t)b * n + gz) * n + gy) * n + gx;
-          float v = acc[i][t][j] + bo;
+        for (int j = 0; j < 4; ++j) {
+          float v = acc[i][t][j] + bo[j];
           if (RELU) v = fmaxf(v, 0.0f);
-          if (a.mask && !(bf(a.mask[idx * COUT + o]) > 0.0f)) v = 0.0f;
-          a.out[idx * COUT + o] = (bf16)v;
+          if (a.mask && !(bf(mk[j]) > 0.0f)) v = 0.0f;
+          r[j] = (bf16)v;
         }
+        *reinterpret_cast<bf16x4*>(a.out + idx) = r;
       }
     }
   }
@@ -822,7 +846,17 @@ template <int CIN, int COUT, int C0, bool RELU>
 hipError_t conv(const bf16* s0, const bf16* s1, const bf16* w, const float* bias, const bf16* mask, bf16* out, int n,
                 int batch, hipStream_t st) {
   ConvArgs a{s0, s1, w, bias, mask, out, n};
-  hipLaunchKernelGGL((k_conv<CIN, COUT, C0, RELU>), dim3(conv_blocks(n, batch)), dim3(NT), 0, st, a);
+  const int nb = conv_blocks(n, batch);
+  constexpr int NTL = COUT / 16;
+  // With fewer bricks than CUs each output tile gets its own blocks (64 to 64
+  // channels on four 16^3 grids, 64 bricks: 28 us with two blocks a brick, 37
+  // with one; one 64^3 region forward 152 us instead of 182).  From 512 bricks
+  // on, staging the input once per brick is the better (96 to 32 channels on
+  // four 32^3 grids 38 us, split 60).
+  if (NTL > 1 && nb < 256)
+    hipLaunchKernelGGL((k_conv<CIN, COUT, C0, 1, RELU>), dim3(nb, NTL), dim3(NT), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_conv<CIN, COUT, C0, NTL, RELU>), dim3(nb), dim3(NT), 0, st, a);
   return launched("k_conv");
 }
 
