@@ -595,7 +595,10 @@ struct XWave {
   static constexpr int RG = 8;                      // elements per lane and component
   static constexpr int LANES = H / RG;
   static constexpr int G = 64 / LANES;              // rows per wave
-  static constexpr int NW = H == 32 ? 1 : H == 64 ? 2 : 4;
+  // waves per block, measured: at 256^3 one wave (nu pass 97 us, mu 82; four
+  // 102 and 90), at 128^3 two (17 us; one 19), at 1024^3 four (6.8 ms; two 7.1,
+  // eight 8.1); at 64^3 it makes no difference
+  static constexpr int NW = H == 32 || H == 128 ? 1 : H == 64 ? 2 : 4;
   static constexpr int NT = 64 * NW;
   static constexpr int ROWS = NW * G;               // rows per block
   static constexpr int XB = H + H / 16;             // padded LDS row (xpad)
