@@ -289,10 +289,15 @@ __global__ __launch_bounds__(256) void k_scatter(int64_t n, const int* __restric
   if (j == 0) flags[1] = (int)n;
 }
 
-__global__ __launch_bounds__(256) void k_fill(float* p, long long count) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-       i += (long long)gridDim.x * blockDim.x)
-    p[i] = 0.0f;
+// 16 bytes a thread between the first and last 16-byte boundary (four-byte
+// stores and a block per 256 of them took 20 us for the 67 MB of a 256^3 box)
+__global__ __launch_bounds__(256) void k_fill(float* p, long long head, long long quads, long long count) {
+  const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x, step = (long long)gridDim.x * blockDim.x;
+  float4* q = reinterpret_cast<float4*>(p + head);
+  for (long long i = i0; i < quads; i += step) q[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const long long tail = head + 4 * quads;
+  if (i0 < head) p[i0] = 0.0f;
+  if (i0 < count - tail) p[tail + i0] = 0.0f;
 }
 
 // ---------------------------------------------------------------------------
@@ -650,9 +655,13 @@ __global__ __launch_bounds__(kNT) void k_diag_phi(KernelGeom kg, const float* __
 // ---------------------------------------------------------------------------
 hipError_t fill_zero(float* p, long long count, hipStream_t st) {
   if (count <= 0) return hipSuccess;
-  long long blocks = (count + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks), dim3(256), 0, st, p, count);
+  long long head = (4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3;   // floats to a 16-byte boundary
+  if (head > count) head = count;
+  const long long quads = (count - head) / 4;
+  long long blocks = (quads + 255) / 256;
+  if (blocks < 1) blocks = 1;
+  if (blocks > 16384) blocks = 16384;
+  hipLaunchKernelGGL(k_fill, dim3((unsigned)blocks), dim3(256), 0, st, p, head, quads, count);
   return hipGetLastError();
 }
 

@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kRedNT) void k_deposit_reduce(KernelGeom kg, const 
 // particles.  65 537 particles of a mixture at sigma = 2 in a 256^3 box: a
 // smooth_accel call takes 134 us, 3000 us with one wave per particle reading
 // six neighbours per cell from memory; the ring (4097 particles, sigma = 1.5)
-// gathers and pushes in 40 us instead of 115 with a lane per particle alone.
+// gathers and pushes in 47 us instead of 115 with a lane per particle alone.
 
 // Acceleration from the summed differences, then the store or the push.
 __device__ __forceinline__ void gather_out(const KernelGeom& kg, int64_t i, double norm, float gx, float gy, float gz,
