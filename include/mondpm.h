@@ -116,9 +116,10 @@ typedef struct {
 typedef struct pm_ctx pm_ctx;
 
 /* Bytes of device memory a context needs for these parameters (the spectra,
- * the Newton potential's spectrum, two real grids, sort buffers for
- * max_particles particles, the tables and, with PM_F_RESIDUAL, tol > 0 or
- * PM_F_WARM_START, the previous iterate of F); 0 for invalid parameters or
+ * the Newton potential's spectrum, two grids that each hold a real field or
+ * one spectrum, sort buffers for max_particles particles, the tables and, with
+ * PM_F_RESIDUAL, tol > 0 or PM_F_WARM_START, the previous iterate of F as a
+ * field or as its spectra); 0 for invalid parameters or
  * max_particles outside [0, 2^30]. */
 size_t pm_workspace_bytes(const pm_params* p, int64_t max_particles);
 

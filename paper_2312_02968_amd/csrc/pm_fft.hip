@@ -382,7 +382,7 @@ __global__ __launch_bounds__(NT) void k_xpass(float2* spec, const float2* spec_i
 //  - nu / mu act on the registers.
 // In the small boxes a block form (rows in LDS, a barrier per stage) took 15, 25
 // and 121 to 150 us for the nu pass at 64^3, 128^3 and 256^3; this form 9.7, 16
-// and 102 us.  Bound: HBM at 256^3 and up, the latency of one wave below.
+// and 97 us.  Bound: HBM at 256^3 and up, the latency of one wave below.
 // No block-wide barrier is needed after the twiddle table is loaded.
 // ----------------------------------------------------------------------------
 __device__ __forceinline__ void wave_sync() {
@@ -586,9 +586,7 @@ __device__ __forceinline__ void fft32_lane4(float2* v, float2* xb, int j, const 
   for (int r = 0; r < 8; ++r) v[r] = t[r];
 }
 
-// Rows of H complex by waves: eight elements per lane and component.  Waves per
-// block: four, one or two in the small boxes, whose few rows would otherwise
-// leave CUs without a block (64^3: 256 waves).
+// Rows of H complex by waves: eight elements per lane and component.
 template <int H>
 struct XWave {
   static constexpr int N = 2 * H;
@@ -1921,8 +1919,13 @@ hipError_t launch_y(const FftGeom& g, float2* spec, int ncomp, hipStream_t st) {
   using C = Cfg<N>;
   constexpr int TY = IO ? 8 : C::TY;                 // FP16: two interleaved sets of 8 columns
   const int tiles = (C::H + 1 + 15) / 16;
+  // FP16 spectra: 64 KB of LDS leave two blocks per CU at 512^3 and one at
+  // 1024^3, so their waves are what hides the loads (0.56 -> 0.42 ms a pass at
+  // 512^3 with 512 threads, a K = 2 increment 12.1 -> 11.3 ms, at 1024^3 156 ->
+  // 136; at 256^3 four blocks of 256 threads are better, 2.5 against 2.9 ms).
+  constexpr int NT = IO && N >= 512 ? 512 : kNT;
   const size_t sh = sizeof(float2) * ((size_t)ColBuf<N, TY>::elems + N);
-  hipLaunchKernelGGL((k_ypass<N, TY, kNT, INV, IO>), dim3(tiles, N, ncomp), dim3(kNT), sh, st, spec,
+  hipLaunchKernelGGL((k_ypass<N, TY, NT, INV, IO>), dim3(tiles, N, ncomp), dim3(NT), sh, st, spec,
                      g.comp_stride, g.ps, C::H + 1, g.tw, g.sc, g.gate);
   return hipGetLastError();
 }
