@@ -58,16 +58,22 @@ def measured_traffic(kernel, workload):
             t = json.load(f)
     except (OSError, ValueError):
         return None
-    if (t.get("source_hash") != source_hash() or t.get("workload") != workload
-            or kernel not in t.get("kernels", {})):
+    if t.get("source_hash") != source_hash() or t.get("workload") != workload:
         return None
-    return t["kernels"][kernel]["bytes_per_launch"]
+    k = t.get("kernels", {})
+    if kernel not in k and kernel in ("z_curl", "z_div"):
+        kernel = "z_pair"                       # one kernel symbol for both projections
+    return k[kernel]["bytes_per_launch"] if kernel in k else None
 
 
 _X_MODES = {0: "x_fwd_real", 1: "x_inv_real", 2: "x_nu", 3: "x_mu", 4: "x_nu_keep", 5: "x_lin_nu", 6: "x_lin_nu_keep",
             7: "x_lin_mu", 8: "x_fwd_coarse3"}
 _Z_OPS = {0: "z_fwd", 1: "z_inv", 2: "z_newton", 3: "z_curl", 4: "z_curl_final", 5: "z_div", 6: "z_newton",
           7: "z_poisson", 8: "z_newton", 9: "z_apparent", 10: "z_grad", 11: "z_newton", 12: "z_poisson"}
+
+# passes in potential form; curl-free and divergence-free projections share one
+_YPOT_OPS = {0: "y_fwd", 1: "y_inv", 2: "y_inv", 3: "y_fwd"}
+_ZPOT_OPS = {0: "z_newton", 1: "z_pair", 2: "z_curl_final", 3: "z_source", 4: "z_newton"}
 
 
 def timer_name(kernel):
@@ -87,6 +93,10 @@ def timer_name(kernel):
     half = lambda name, io: name + "_h" if int(io) else name
     if base == "k_ypass":                   # <L, T, NT, INV, IO>
         return half("y_inv" if args[3] == "true" else "y_fwd", args[4])
+    if base == "k_ypot":                    # <L, T, NT, YOP>
+        return _YPOT_OPS.get(int(args[3]), base)
+    if base == "k_zpot":                    # <L, T, NT, ZOP>
+        return _ZPOT_OPS.get(int(args[3]), base)
     if base == "k_ypass_mfma":              # <L, INV>
         return "y_inv" if args[1] == "true" else "y_fwd"
     if base == "k_xpass_wave":              # <H, XMODE, NC, IO>
@@ -320,21 +330,26 @@ def increment_bytes(N, K, half):
     fixed K, no residual) by the same counting as pass_bytes: complex entries
     of 4 bytes (FP16 spectra) or 8 (FP32); the Newton spectrum of d_rho and
     the last one-component spectrum stay FP32; the linearised x passes also
-    read the base field (3 R1)."""
+    read the base field (3 R1).  FP32 spectra run in potential form (see
+    pass_bytes), FP16 ones as three components."""
     C1 = N * N * (N // 2 + 1)
     e = 4 if half else 8
     Ch, Cf = C1 * e, C1 * 8
     R1 = N ** 3 * 4
     b = R1 + Cf                       # x_fwd_real of d_rho
     b += 2 * Cf                       # y_fwd, one component, FP32
+    b += K * (6 * Ch + 3 * R1)        # x(linearised nu)
+    b += 2 * Cf + Cf + R1             # y_inv (one component) and x_inv_real
+    if not half:
+        b += 4 * Cf + 5 * Cf          # z_newton and y_inv
+        b += K * 5 * Cf               # y_fwd
+        b += (K - 1) * ((4 + 5 + 6 + 6 + 4 + 8) * Cf + 3 * R1)   # z, y, x(mu), y, z(div), y
+        return b + 3 * Cf             # z_curl_final
     b += Cf + Cf + 3 * Ch             # z_newton: rho_hat in, phi_N_hat and dg_N out
     b += 6 * Ch                       # y_inv
-    b += K * (6 * Ch + 3 * R1)        # x(linearised nu)
     b += K * 6 * Ch                   # y_fwd
     b += (K - 1) * (6 * Ch + 6 * Ch + 6 * Ch + 3 * R1 + 6 * Ch + 6 * Ch + Cf + 6 * Ch)  # z, y, x(mu), y, z(div), y
-    b += 3 * Ch + Cf                  # z_curl_final
-    b += 2 * Cf + Cf + R1             # y_inv (one component) and x_inv_real
-    return b
+    return b + 3 * Ch + Cf            # z_curl_final
 
 
 def incremental_record(w, K=2, reps=10):
@@ -401,14 +416,19 @@ def make_workload(name):
     raise SystemExit(f"unknown workload {name}")
 
 
-def pass_bytes(N, K):
+def pass_bytes(N, K, pair=True):
     """Algorithmic HBM bytes per step of each timed kernel kind, and launches per step.
 
     One complex spectrum component holds N * N * (N/2 + 1) valid entries of 8
     bytes (C1); a real grid holds N^3 floats (R1).  Each pass reads its input
     once and writes its output once.  The launch sequence is the one of one
-    fixed-K solve: Newton (x, y, z, y), then per iteration x(nu), y, z(curl),
-    y, x(mu), y, z(div), y, and in the last iteration x(nu), y, z(final).
+    fixed-K solve from the zero start: Newton (x, y, z, y), then per iteration
+    x(nu), y, z(curl), y, x(mu), y, z(div), y, and in the last iteration
+    x(nu), y, z(final).  In potential form (pair, the FP32 transforms) the z
+    passes work on a pair of spectra: forward y passes read three components
+    and write two (before z(div) they also read the kept k . g_N), inverse y
+    passes read two and write three (after z(div) adding to the three of F'),
+    z(newton) writes the kept k . g_N beside the pair.
     """
     C1 = N * N * (N // 2 + 1) * 8
     R1 = N ** 3 * 4
@@ -417,12 +437,20 @@ def pass_bytes(N, K):
     b["x_inv_real"] = (C1 + R1, 1)
     b["x_nu"] = (K * 6 * C1, K)
     b["x_mu"] = ((K - 1) * 6 * C1, K - 1)
-    b["y_fwd"] = (2 * C1 + (2 * (K - 1) + 1) * 6 * C1, 2 * (K - 1) + 2)
-    b["y_inv"] = (6 * C1 + 2 * (K - 1) * 6 * C1 + 2 * C1, 2 * (K - 1) + 2)
-    b["z_newton"] = (C1 + C1 + 3 * C1, 1)
-    b["z_curl"] = ((K - 1) * 6 * C1, K - 1)
-    b["z_div"] = ((K - 1) * 7 * C1, K - 1)
-    b["z_curl_final"] = (3 * C1 + C1, 1)
+    if pair:
+        b["y_fwd"] = ((2 + K * 5 + (K - 1) * 6) * C1, 2 * K)
+        b["y_inv"] = ((5 + (K - 1) * (5 + 8) + 2) * C1, 2 * K)
+        b["z_newton"] = (4 * C1, 1)
+        b["z_curl"] = ((K - 1) * 4 * C1, K - 1)
+        b["z_div"] = ((K - 1) * 4 * C1, K - 1)
+        b["z_curl_final"] = (3 * C1, 1)
+    else:
+        b["y_fwd"] = (2 * C1 + (2 * (K - 1) + 1) * 6 * C1, 2 * K)
+        b["y_inv"] = (6 * C1 + 2 * (K - 1) * 6 * C1 + 2 * C1, 2 * K)
+        b["z_newton"] = (C1 + C1 + 3 * C1, 1)
+        b["z_curl"] = ((K - 1) * 6 * C1, K - 1)
+        b["z_div"] = ((K - 1) * 7 * C1, K - 1)
+        b["z_curl_final"] = (3 * C1 + C1, 1)
     b["fill"] = (R1, 1)
     return b
 
@@ -668,7 +696,7 @@ def main():
 
     Npad = p["n_pad"]
     K = p["iters"]
-    pb = pass_bytes(Npad, K)
+    pb = pass_bytes(Npad, K, pair=a.dft == "fp32")
     dom = max((k for k in timing if k in pb), key=lambda k: timing[k][0])
     tot_ms, launches = timing[dom]
     bytes_step, launches_step = pb[dom]
@@ -683,8 +711,10 @@ def main():
                 extra = f"  {bb / 1e9:.3f} GB/launch  {bb / (t / c * 1e-3) / 1e9:.0f} GB/s"
             print(f"{k:14s} {t / a.steps:8.3f} ms/step  {c // a.steps:3d} launches/step  "
                   f"{t / c:8.4f} ms/launch{extra}", file=sys.stderr)
+    # the counters are of the zero start with FP32 transforms
+    traffic = measured_traffic(dom, w["workload"]) if a.dft == "fp32" and not a.warm else None
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(dom, w["workload"]), "kernel": dom,
+            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": dom,
             "avg_launch_ms": round(avg_ms, 4), "algorithmic_bytes_per_launch": int(bytes_launch)}
     # particle kernels against the HBM roofline: algorithmic bytes 16 N + 4 n^3
     # (positions and masses read, the physical region of rho written) for the
